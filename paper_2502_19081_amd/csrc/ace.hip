@@ -1752,8 +1752,8 @@ static size_t blocks_lds(const Ctx &c, int ta, size_t tsz, int stage_w)
 }
 
 // Launch shape of the order-3 blocks: MFMA stages for single-species FP32
-// models (FP64, the verification precision, and multi-species models keep
-// the VALU stages); tile of c.ace_tile atoms (default 4) with the block's
+// models (FP64 models of several species and multi-species models keep the
+// VALU stages); tile of c.ace_tile atoms (default 4) with the block's
 // weights staged in LDS (c.ace_stage_w, default on) — the best of a sweep
 // over 1-8 atoms with and without staging on the 8,193-atom workload; the
 // tile shrinks until the LDS tile fits 64 KiB.
@@ -1782,6 +1782,8 @@ static void contract_t(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
             launch_ace_o3w(s, c, ws, L, species);
         else
             launch_ace_o3(s, c, ws, L);
+    } else if (a.order >= 3 && c.m.n_pb > 0 && c.o3 == 3) {
+        launch_ace_o3d(s, c, ws, L);
     } else if (a.order >= 3 && c.m.n_pb > 0) {
         int TA, mf, stage;
         blocks_shape(c, sizeof(T), TA, mf, stage);

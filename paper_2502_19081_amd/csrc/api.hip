@@ -336,10 +336,12 @@ struct HostTables {
     int dp_stride = 0;
     // matrix-core order-3 kernel
     bool o3 = false;
-    int o3_kind = 0;  // 1 single-species narrow form, 2 wide form
+    int o3_kind = 0;  // 1 single-species narrow form, 2 wide form, 3 FP64 form
     bool o3_wide_ready = false;  // wide-form weight fragments built
     std::vector<double> o3ww;
     std::vector<int32_t> o3wwb;  // BF16 wide-form fragments, two values per int
+    std::vector<O3DGroup> o3dg;  // FP64 form
+    std::vector<double> o3dw;
     int o3_nch2 = 0;
     std::vector<double> o3g, o3w, o3sw, o3gs;
     std::vector<int> o3o, o3mt, o3mtv, o3base, o3order, o3wbeg;
@@ -538,6 +540,116 @@ static uint32_t bf16_bits(float f)
     return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
 
+// Work items of a tile's block list over nb bins: an item is a range of m3
+// rows of one block (item code: block | first row << 16 | end row << 24), a
+// block costing more than cap cut into row ranges of about that cost; longest
+// first onto the least loaded bin, each bin in (block, first row) order.
+static std::vector<std::vector<int>> assign_bins(const std::vector<int> &cost,
+                                                 const std::vector<std::vector<int>> &rcost, int nb,
+                                                 long cap)
+{
+    std::vector<std::pair<long, int>> items;  // (cost, code)
+    for (size_t p = 0; p < cost.size(); ++p) {
+        const int d3 = (int)rcost[p].size();
+        const int k = (int)std::min<long>(d3, (cost[p] + cap - 1) / cap);
+        int lo = 0;
+        for (int part = 0; part < k; ++part) {
+            const int hi = lo + (d3 - lo) / (k - part);  // near-even row counts
+            long cst = 0;
+            for (int r = lo; r < hi; ++r)
+                cst += rcost[p][r];
+            items.push_back({cst, (int)p | (lo << 16) | (hi << 24)});
+            lo = hi;
+        }
+    }
+    std::stable_sort(items.begin(), items.end(),
+                     [](const std::pair<long, int> &x, const std::pair<long, int> &y) {
+                         return x.first > y.first;
+                     });
+    std::vector<std::vector<int>> lists(nb);
+    std::vector<long> load(nb, 0);
+    for (const auto &it : items) {
+        int w = 0;
+        for (int k = 1; k < nb; ++k)
+            if (load[k] < load[w])
+                w = k;
+        lists[w].push_back(it.second);
+        load[w] += it.first;
+    }
+    for (std::vector<int> &l : lists)
+        std::sort(l.begin(), l.end(), [](int x, int y) {
+            const int px = x & 0xffff, py = y & 0xffff;
+            return px != py ? px < py : ((x >> 16) & 0xff) < ((y >> 16) & 0xff);
+        });
+    return lists;
+}
+
+// Tables of the FP64 order-3 form (single species, at most 16 channels):
+//  - per (block, m3) the Gaunt entries in groups of up to two that share m1
+//    (a real (m1, m3) couples to at most two m2), (first group, count) in o3mt;
+//  - weight fragments: lane (c = l % 16, q = l / 16) owns the quarter of the
+//    channel pairs a in H (q / 2) + [0, H), b in H (q % 2) + [0, H), H = nchp / 2,
+//    and step s = H i + j holds W[a = H (q / 2) + i][b = H (q % 2) + j][c];
+//  - the blocks over 4 G bins, G = 1 .. 16, as the other forms.
+static void build_o3d(const mlmix_model_desc &d, HostTables &t)
+{
+    const int nch = d.ace_n_rad, nchp = (nch + 3) & ~3, H = nchp / 2;
+    const size_t P = t.pb.size();
+    std::vector<int> cost(P, 0);
+    std::vector<std::vector<int>> rcost(P);
+    for (size_t p = 0; p < P; ++p) {
+        const PBlock &b = t.pb[p];
+        t.o3base.push_back((int)t.o3mt.size() / 2);
+        for (int m3 = 0; m3 < 2 * b.l3 + 1; ++m3) {
+            const int first = (int)t.o3dg.size();
+            for (int e = t.gm3[b.gm3_off + m3]; e < t.gm3[b.gm3_off + m3 + 1]; ++e) {
+                const int o1 = t.gofs[e] & 0xffff, o2 = t.gofs[e] >> 16;
+                O3DGroup *g = (int)t.o3dg.size() > first ? &t.o3dg.back() : nullptr;
+                if (g && g->o1 == o1 && g->gb == 0.0) {
+                    g->o2b = o2;
+                    g->gb = t.gval[e];
+                } else {
+                    t.o3dg.push_back(O3DGroup{o1, o2, o2, 0, t.gval[e], 0.0});
+                }
+            }
+            const int ng = (int)t.o3dg.size() - first;
+            if (ng == 0)
+                return;  // an empty row: keep the general kernel
+            t.o3mt.push_back(first);
+            t.o3mt.push_back(ng);
+            // in units of one 16x16x4 FP64 matrix step (64 cycles; a vector
+            // instruction takes four)
+            const int rc = ng * (H * H + 2 * H) / 16 + H * H + 4;
+            cost[p] += rc;
+            rcost[p].push_back(rc);
+        }
+    }
+    long total = 0;
+    for (int v : cost)
+        total += v;
+    t.o3dw.assign(P * H * H * 64, 0.0);
+    for (size_t p = 0; p < P; ++p)
+        for (int st = 0; st < H * H; ++st)
+            for (int l = 0; l < 64; ++l) {
+                const int c = l & 15, q = l >> 4;
+                const int a = H * (q >> 1) + st / H, b = H * (q & 1) + st % H;
+                if (a < nch && b < nch && c < nch)
+                    t.o3dw[(p * H * H + st) * 64 + l] =
+                        t.W[t.pb[p].w_off + ((size_t)a * nchp + b) * nchp + c];
+            }
+    for (int G = 1; G <= kO3MaxSplit; G <<= 1) {
+        const int nb = 4 * G;
+        const long cap = G == 1 ? total : std::max<long>(1, total / nb / 2);
+        for (const std::vector<int> &l : assign_bins(cost, rcost, nb, cap)) {
+            t.o3wbeg.push_back((int)t.o3order.size());
+            t.o3order.insert(t.o3order.end(), l.begin(), l.end());
+        }
+        t.o3wbeg.push_back((int)t.o3order.size());
+    }
+    t.o3 = true;
+    t.o3_kind = 3;
+}
+
 static void build_o3(const mlmix_model_desc &d, HostTables &t, int waves)
 {
     const int nch = d.n_species * d.ace_n_rad, lmax = d.ace_lmax;
@@ -545,8 +657,13 @@ static void build_o3(const mlmix_model_desc &d, HostTables &t, int waves)
     const bool reduced = d.precision == MLMIX_BF16_CONTRACT || d.precision == MLMIX_FP8_CONTRACT;
     t.o3 = false;
     t.o3_kind = 0;
-    if (d.ace_order < 3 || t.pb.empty() || d.precision == MLMIX_FP64)
+    if (d.ace_order < 3 || t.pb.empty())
         return;
+    if (d.precision == MLMIX_FP64) {
+        if (d.n_species == 1 && nch <= 16)
+            build_o3d(d, t);
+        return;
+    }
     const bool narrow_ok = d.n_species == 1 && nch <= 16;
     const bool wide_ok = !narrow_ok && nch <= 32 &&
                          (d.precision == MLMIX_FP32 || d.precision == MLMIX_BF16_CONTRACT);
@@ -741,41 +858,10 @@ static void build_o3(const mlmix_model_desc &d, HostTables &t, int waves)
         const int nb = (kind == 1 ? waves : 4) * G;
         // one workgroup per tile (large S): whole blocks (measured faster)
         const long cap = G == 1 ? total : std::max<long>(1, total / nb / 2);
-        std::vector<std::pair<long, int>> items;  // (cost, code)
-        for (size_t p = 0; p < P; ++p) {
-            const int d3 = (int)rcost[p].size();
-            const int k = (int)std::min<long>(d3, (cost[p] + cap - 1) / cap);
-            int lo = 0;
-            for (int part = 0; part < k; ++part) {
-                const int hi = lo + (d3 - lo) / (k - part);  // near-even row counts
-                long cst = 0;
-                for (int r = lo; r < hi; ++r)
-                    cst += rcost[p][r];
-                items.push_back({cst, (int)p | (lo << 16) | (hi << 24)});
-                lo = hi;
-            }
-        }
-        std::stable_sort(items.begin(), items.end(),
-                         [](const std::pair<long, int> &x, const std::pair<long, int> &y) {
-                             return x.first > y.first;
-                         });
-        std::vector<std::vector<int>> lists(nb);
-        std::vector<long> load(nb, 0);
-        for (const auto &it : items) {
-            int w = 0;
-            for (int k = 1; k < nb; ++k)
-                if (load[k] < load[w])
-                    w = k;
-            lists[w].push_back(it.second);
-            load[w] += it.first;
-        }
+        std::vector<std::vector<int>> lists = assign_bins(cost, rcost, nb, cap);
         for (int w = 0; w < nb; ++w) {
             t.o3wbeg.push_back((int)t.o3order.size());  // absolute offsets
             t.o3rbeg.push_back((int)t.o3rowv.size() / 4);
-            std::sort(lists[w].begin(), lists[w].end(), [](int x, int y) {
-                const int px = x & 0xffff, py = y & 0xffff;
-                return px != py ? px < py : ((x >> 16) & 0xff) < ((y >> 16) & 0xff);
-            });
             t.o3order.insert(t.o3order.end(), lists[w].begin(), lists[w].end());
             if (runs)
                 continue;
@@ -1062,6 +1148,8 @@ static std::vector<char> pack(const HostTables &t, DevModel &m)
     append<float>(blob, m.o3w, t.o3w);
     append<float>(blob, m.o3ww, t.o3ww);
     append_raw(blob, m.o3wwb, t.o3wwb);
+    append_raw(blob, m.o3dg, t.o3dg);
+    append<double>(blob, m.o3dw, t.o3dw);
     append<float>(blob, m.o3sw, t.o3sw);
     append_raw(blob, m.o3order, t.o3order);
     append_raw(blob, m.o3wbeg, t.o3wbeg);
@@ -1429,6 +1517,10 @@ try {
     if (c.o3 == 2 && (o3w_lds_bytes(c) > (size_t)c.max_lds || o3w_prepare(c) != hipSuccess)) {
         (void)hipGetLastError();
         c.o3 = 0;  // the wide form does not fit this device: VALU blocks
+    }
+    if (c.o3 == 3 && (o3d_lds_bytes(c) > (size_t)c.max_lds || o3d_prepare(c) != hipSuccess)) {
+        (void)hipGetLastError();
+        c.o3 = 0;
     }
     if ((c.qmode == 2 && c.o3 != 1) || (c.qmode == 1 && c.o3 == 0)) {
         return fail(MLMIX_E_ARG, "the FP8 contraction mode needs a single-species model with at "

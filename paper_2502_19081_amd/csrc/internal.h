@@ -156,6 +156,7 @@ struct DevModel {
     size_t o3o, o3mt, o3mtv, o3rowv, o3rbeg, o3wr, o3base, o3w, o3sw, o3order, o3wbeg, o3gs;
     size_t o3ww;   // weight fragments of the wide form
     size_t o3wwb;  // its BF16 fragments (BF16 mode: eight values per lane and 32-deep step)
+    size_t o3dg, o3dw;  // FP64 form: Gaunt groups, weight fragments [block][step][lane]
     int dp_stride;  // partial-D entries per S atom (sum over blocks of nchan*(2 l3 + 1))
     // partial-D column lists: set k at dsum + dsum_off[k] holds L2 + 1 run
     // offsets, then the columns (atom-relative, channel 0) summed into each
@@ -178,6 +179,15 @@ struct DSumSel {
     int grid, max_split;
 };
 
+// One Gaunt group of the FP64 order-3 form: up to two entries (m1, m2) of a
+// (block, m3) row that share the first A row (o1); offsets in doubles into the
+// atom's staged A, a missing second entry has gb = 0.
+struct O3DGroup {
+    int o1, o2a, o2b, pad;
+    double ga, gb;
+};
+static_assert(sizeof(O3DGroup) == 32, "O3DGroup is one 32-byte scalar load");
+
 // One (l1 <= l2, l3) block of the order-3 contraction.
 struct PBlock {
     int l1, l2, l3;
@@ -197,7 +207,8 @@ struct Ctx {
     int max_ent_pb;        // Gaunt entries of the largest single block
     // order-3 contraction on the matrix cores: 0 no (VALU blocks), 1 the
     // single-species form (<= 16 channels, FP32/BF16/FP8 operands), 2 the wide
-    // form (FP32, any species count, <= 32 channels)
+    // form (FP32, any species count, <= 32 channels), 3 the FP64 form (single
+    // species, <= 16 channels)
     int o3 = 0;
     int max_lds = 65536;   // dynamic LDS a workgroup may use on this device
     int basis_mfma = 1;    // atomic basis and pair adjoint on the matrix cores (FP32)
@@ -313,6 +324,9 @@ void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
                     const int32_t *species, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 size_t o3w_lds_bytes(const Ctx &c);
 hipError_t o3w_prepare(const Ctx &c);
+void launch_ace_o3d(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L);
+size_t o3d_lds_bytes(const Ctx &c);
+hipError_t o3d_prepare(const Ctx &c);
 
 // ---- uf3.hip ----
 // mask_flags: NULL, or the flags array (MLMIX_CHEAP_MASKED): the cheap

@@ -1097,6 +1097,266 @@ void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
     }
 }
 
+// ------------------------------------------------------------- FP64 form
+//
+// The contraction for single-species FP64 models of at most 16 channels: the
+// tiles of 16 atoms, bins and per-(block, m3) partial-D columns of the forms
+// above, with an FP64 matrix-core dense stage.
+//
+//  lane (t = atom, q):  P_t[a][b] for its quarter of the channel pairs, a in
+//                       H (q / 2) + [0, H), b in H (q % 2) + [0, H), H = nchp / 2.
+//                       The Gaunt entries of a row come in groups that share
+//                       m1: b' = ga A[l2 m2a] + gb A[l2 m2b] first, then one
+//                       outer product A[l1 m1] x b', so that two entries cost
+//                       one pass of H^2 multiply-adds;
+//  dense stage:         D[t][c] = sum P_t[a][b] W[a][b][c], H^2 16x16x4 FP64
+//                       steps in two accumulators (lane (c, q) supplies the
+//                       weight of the same pair; result row 4 v + q, column
+//                       lane % 16).
+//
+// Bound by the FP64 matrix steps (64 cycles each, nchp / 16 of the columns
+// used) with the vector stage of the other wave of the SIMD beside them. The
+// groups are read as scalar loads, the atom stride keeps the 16 atoms' 16-byte
+// reads in distinct banks, and up to 12 channels a block's weights stay in
+// registers over its rows.
+// FP64, 12 channels, lmax 4, 2,000 atoms in S: 46 us per launch, 31 TFLOP/s of
+// the 72 that a large FP64 product reaches here (the vector-ALU block kernel
+// that it replaces: 660 us).
+struct O3DArgs {
+    const int *wbeg;    // per split G: 4 G + 1 bin offsets into order
+    int nch, L2, dp_stride;
+};
+
+typedef double d4v __attribute__((ext_vector_type(4)));
+typedef double d2v __attribute__((ext_vector_type(2)));
+
+// LDS doubles per atom: a multiple of 32 (one 256-byte bank row) plus two
+__host__ __device__ constexpr int o3d_stride(int kat) { return ((kat + 31) & ~31) + 2; }
+
+template <int NC>
+__global__ void __launch_bounds__(256, 2)
+    k_ace_o3d(const int *__restrict__ hdr, O3DArgs a, const double *__restrict__ wfrag,
+              const O3DGroup *__restrict__ grp,
+              const int *__restrict__ mt, const int *__restrict__ base,
+              const int *__restrict__ order, const int *__restrict__ dp_off,
+              const double *__restrict__ A, double *__restrict__ Dpart)
+{
+    constexpr int H = NC / 2, KS = H * H;
+    // up to 12 channels a block's weights stay in registers over its rows and
+    // the A values of the next group are read while one is accumulated (two
+    // register sets); 16 channels have registers for neither
+    constexpr bool HOLD = NC <= 12;
+    constexpr int NS = HOLD ? 2 : 1, CH = KS < 8 ? KS : 8;
+    const int nS = hdr[H_NS];
+    const int ntile = (nS + kO3Atoms - 1) / kO3Atoms;
+    // the largest split whose items still run in one round of workgroups
+    int G = 1, lg = 0;
+    while (G < kO3MaxSplit && 2 * ntile * G <= (int)gridDim.x) {
+        G <<= 1;
+        ++lg;
+    }
+    const int nitem = ntile * G;
+    const int vb = xcd_major(blockIdx.x, gridDim.x);
+    if (vb >= nitem)
+        return;  // uniform across the workgroup
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = lane & 15, q = lane >> 4;
+    const int kat = a.L2 * NC, astr = o3d_stride(kat);
+    extern __shared__ __align__(16) char smem_raw[];
+    double *At = reinterpret_cast<double *>(smem_raw);  // [16][astr]
+    const double *Aa = At + m * astr + H * (q >> 1), *Ab = At + m * astr + H * (q & 1);
+    const int *wbeg = a.wbeg + 4 * (G - 1) + lg;
+
+    for (int item = vb; item < nitem; item += gridDim.x) {
+        const int tile = item >> lg, bin = ((item & (G - 1)) << 2) + wv;
+        const int w_lo = wbeg[bin], w_hi = wbeg[bin + 1];
+        const int s0 = tile * kO3Atoms;
+        const int na = min(kO3Atoms, nS - s0);
+        __syncthreads();  // every wave is done with the previous tile's A
+        for (int r = tid; r < kO3Atoms * (kat / 2); r += 256) {
+            const int t = r / (kat / 2), e = 2 * (r - t * (kat / 2));
+            *reinterpret_cast<d2v *>(At + t * astr + e) =
+                t < na ? *reinterpret_cast<const d2v *>(A + (size_t)(s0 + t) * kat + e) : (d2v){0.0, 0.0};
+        }
+        __syncthreads();
+        for (int wi = w_lo; wi < w_hi; ++wi) {
+            const int code = order[wi];
+            const int p = code & 0xffff, m3lo = (code >> 16) & 0xff, m3hi = (code >> 24) & 0xff;
+            const int rbase = base[p];
+            const double *wblk = wfrag + (size_t)p * KS * 64;  // uniform base, lane offset
+            double *Dblk = Dpart + dp_off[p];
+            double wf[HOLD ? KS : 1];
+            if constexpr (HOLD)
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    wf[s] = wblk[s * 64 + (unsigned)lane];
+            for (int m3 = m3lo; m3 < m3hi; ++m3) {
+                const int g0 = mt[2 * (rbase + m3)], ng = mt[2 * (rbase + m3) + 1];
+                double P[H][H] = {};
+                d2v x1[NS][H / 2], xa[NS][H / 2], xb[NS][H / 2];
+                double ga[NS], gb[NS];
+                auto load = [&](int k, int h) {
+                    const O3DGroup g = grp[g0 + min(k, ng - 1)];  // uniform: scalar loads
+                    ga[h] = g.ga;
+                    gb[h] = g.gb;
+#pragma unroll
+                    for (int i = 0; i < H / 2; ++i) {
+                        x1[h][i] = reinterpret_cast<const d2v *>(Aa + g.o1)[i];
+                        xa[h][i] = reinterpret_cast<const d2v *>(Ab + g.o2a)[i];
+                        xb[h][i] = reinterpret_cast<const d2v *>(Ab + g.o2b)[i];
+                    }
+                };
+                auto accumulate = [&](int h, bool first) {
+#pragma unroll
+                    for (int j = 0; j < H; ++j) {
+                        const double bv = fma(gb[h], xb[h][j / 2][j % 2], ga[h] * xa[h][j / 2][j % 2]);
+#pragma unroll
+                        for (int i = 0; i < H; ++i)
+                            P[i][j] = first ? x1[h][i / 2][i % 2] * bv
+                                            : fma(x1[h][i / 2][i % 2], bv, P[i][j]);
+                    }
+                };
+                // every row has at least one group (host check)
+                if constexpr (HOLD) {
+                    load(0, 0);
+                    load(1, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    accumulate(0, true);
+                    for (int k = 1; k < ng; k += 2) {
+                        load(k + 1, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        accumulate(1, false);
+                        if (k + 1 >= ng)
+                            break;
+                        load(k + 2, 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        accumulate(0, false);
+                    }
+                } else {
+                    // a pair of columns b at a time, so that few A values are live
+                    for (int k = 0; k < ng; ++k) {
+                        const O3DGroup g = grp[g0 + k];
+                        d2v y1[H / 2];
+#pragma unroll
+                        for (int i = 0; i < H / 2; ++i)
+                            y1[i] = reinterpret_cast<const d2v *>(Aa + g.o1)[i];
+#pragma unroll
+                        for (int j2 = 0; j2 < H / 2; ++j2) {
+                            const d2v ya = reinterpret_cast<const d2v *>(Ab + g.o2a)[j2];
+                            const d2v yb = reinterpret_cast<const d2v *>(Ab + g.o2b)[j2];
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int jj = 0; jj < 2; ++jj) {
+                                const double bv = fma(g.gb, yb[jj], g.ga * ya[jj]);
+#pragma unroll
+                                for (int i = 0; i < H; ++i)
+                                    P[i][2 * j2 + jj] = fma(y1[i / 2][i % 2], bv, P[i][2 * j2 + jj]);
+                            }
+                        }
+                    }
+                }
+                d4v acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
+                if constexpr (HOLD) {
+#pragma unroll
+                    for (int s = 0; s < KS; s += 2) {
+                        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(P[s / H][s % H], wf[s], acc0, 0, 0, 0);
+                        if (s + 1 < KS)
+                            acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(s + 1) / H][(s + 1) % H],
+                                                                        wf[s + 1], acc1, 0, 0, 0);
+                    }
+                } else {
+                    // weights from the cache, CH steps ahead of their use (an
+                    // opaque pointer: read per row, not all kept over the rows)
+                    const double *wrow = wblk;
+                    asm volatile("" : "+s"(wrow));
+                    double wc[2][CH];
+#pragma unroll
+                    for (int u = 0; u < CH; ++u)
+                        wc[0][u] = wrow[u * 64 + (unsigned)lane];
+#pragma unroll
+                    for (int s0v = 0; s0v < KS; s0v += CH) {
+                        const int cur = (s0v / CH) & 1;
+                        if (s0v + CH < KS)
+#pragma unroll
+                            for (int u = 0; u < CH; ++u)
+                                wc[cur ^ 1][u] = wrow[(s0v + CH + u) * 64 + (unsigned)lane];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int u = 0; u < CH; u += 2) {
+                            const int s = s0v + u;
+                            acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(P[s / H][s % H], wc[cur][u],
+                                                                        acc0, 0, 0, 0);
+                            acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                                P[(s + 1) / H][(s + 1) % H], wc[cur][u + 1], acc1, 0, 0, 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int t = 4 * v + q;
+                    if (t < na && m < a.nch)
+                        Dblk[(size_t)(s0 + t) * a.dp_stride + m3 * a.nch + m] = acc0[v] + acc1[v];
+                }
+            }
+        }
+    }
+}
+
+size_t o3d_lds_bytes(const Ctx &c)
+{
+    return (size_t)kO3Atoms * o3d_stride(c.m.KAt) * sizeof(double);
+}
+
+template <typename F>
+static auto o3d_by_width(int nchp, F &&f)
+{
+    switch (nchp) {
+    case 4: return f(k_ace_o3d<4>);
+    case 8: return f(k_ace_o3d<8>);
+    case 12: return f(k_ace_o3d<12>);
+    default: return f(k_ace_o3d<16>);
+    }
+}
+
+// Lets the FP64 kernel of this model use its dynamic LDS (above 64 KiB from
+// 16 channels at lmax 5 on).
+hipError_t o3d_prepare(const Ctx &c)
+{
+    return o3d_by_width(c.m.nchp, [&](auto *k) {
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(k),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)o3d_lds_bytes(c));
+    });
+}
+
+void launch_ace_o3d(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L)
+{
+    const DevModel &m = c.m;
+    const char *base = static_cast<const char *>(m.base);
+    O3DArgs a;
+    a.wbeg = reinterpret_cast<const int *>(base + m.o3wbeg);
+    a.nch = m.nchan;
+    a.L2 = m.L2;
+    a.dp_stride = m.dp_stride;
+    const size_t lds = o3d_lds_bytes(c);
+    // two workgroups per CU (two waves per SIMD by registers), one when the
+    // tile takes more than half of the LDS
+    const int per_cu = lds <= 80 * 1024 ? 2 : 1;
+    const long items = (((long)L.n + kO3Atoms - 1) / kO3Atoms) * kO3MaxSplit;
+    const int grid = (int)std::min<long>(std::max<long>(items, 1), 256L * per_cu);
+    o3d_by_width(m.nchp, [&](auto *k) {
+        k<<<grid, 256, lds, s>>>(at<int>(ws, L.hdr), a,
+                                 reinterpret_cast<const double *>(base + m.o3dw),
+                                 reinterpret_cast<const O3DGroup *>(base + m.o3dg),
+                                 reinterpret_cast<const int *>(base + m.o3mt),
+                                 reinterpret_cast<const int *>(base + m.o3base),
+                                 reinterpret_cast<const int *>(base + m.o3order),
+                                 reinterpret_cast<const int *>(base + m.dpoff), at<double>(ws, L.A),
+                                 at<double>(ws, L.dpart));
+    });
+}
+
 size_t o3_lds_bytes(const Ctx &c)
 {
     const DevModel &m = c.m;
