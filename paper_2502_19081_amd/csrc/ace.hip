@@ -18,6 +18,8 @@
 //                 g_ij = dE_i/dd_ij = sum_{n,lm} dE/dA (R_n' u Y + R_n grad Y),
 //                 recomputing R, Y and grad Y instead of storing them.
 // Forces follow from g in the gather kernel: F_i = sum_j (g_ij - g_ji).
+#include <type_traits>
+
 #include "internal.h"
 #include "basis.h"
 
@@ -63,6 +65,31 @@ __device__ __forceinline__ double norm2_d(const double d[3])
 }
 
 constexpr int kMaxOwn = 16;  // (lm, channel) entries per lane: L2 * nchp <= 1024
+
+// 16-wide tiles of the harmonics up to lmax = LM. The kernels below are
+// compiled per lmax (0 .. 6): with a runtime lmax the harmonics' control (a
+// loop, a switch and a normalisation load between any two of them) set the
+// length of each wave's serial chain. Same bits in FP32. FP64, 2,000 atoms in
+// S (lmax 4): basis 47 -> 17 us (with the matrix-core form), vector pair
+// adjoint 37 -> 14 us; FP32: all-expensive step of 8,192 atoms 262 -> 246 us,
+// mixed step of 1,023,800 atoms 3.6 % shorter.
+__host__ __device__ constexpr int lm_tiles(int LM) { return ((LM + 1) * (LM + 1) + 15) / 16; }
+
+// f(integral_constant<lmax>) for a model's lmax
+template <typename F>
+static void by_lmax(int lmax, F &&f)
+{
+    switch (lmax) {
+    case 0: f(std::integral_constant<int, 0>()); break;
+    case 1: f(std::integral_constant<int, 1>()); break;
+    case 2: f(std::integral_constant<int, 2>()); break;
+    case 3: f(std::integral_constant<int, 3>()); break;
+    case 4: f(std::integral_constant<int, 4>()); break;
+    case 5: f(std::integral_constant<int, 5>()); break;
+    default: f(std::integral_constant<int, 6>()); break;
+    }
+}
+static_assert(kMaxLmax == 6, "by_lmax covers every lmax");
 
 // wpb atoms per block (one wavefront each). The neighbour-chunk loop runs to
 // the block's longest row so that the waves meet at every barrier.
@@ -175,6 +202,15 @@ struct Mfma<float> {
     static __device__ __forceinline__ v4 op(float x, float y, v4 c)
     {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0);
+    }
+};
+
+template <>
+struct Mfma<double> {
+    typedef double v4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ v4 op(double x, double y, v4 c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0);
     }
 };
 
@@ -562,98 +598,117 @@ __global__ void __launch_bounds__(256)
     }
 }
 
-template <typename T, bool SEG>
+// Pair adjoint in FP64, one wave per S atom: the row's valid pairs (partner in
+// S, inside the cutoff) are listed in LDS by ballot, then the lanes take them
+// 64 at a time; invalid slots get a zero gradient from their owner lane. Bound
+// by the serial chain of one pair (geometry, radial recurrence, harmonics with
+// 2 NR multiply-adds each) at the few waves an FP64 system has: lmax and the
+// usual radial counts are compiled in (NR = 0: a runtime count), so that the
+// chain holds no loop control and the dE/dA reads pair up.
+// 2,000 atoms in S, lmax 4, 12 radial functions: 37 -> 14 us.
+template <int LM, int NR, bool SEG>
 __global__ void __launch_bounds__(256)
-    k_ace_pairgrad(const double *__restrict__ pos, int n, Box b0, const int32_t *__restrict__ species,
-                   int cap, const int *__restrict__ nbr, const int *__restrict__ cnt,
-                   const int *__restrict__ S_idx, const int *__restrict__ S_local,
-                   const int *__restrict__ hdr, AceArgs<T> a, int wpb, const T *__restrict__ dEdA,
-                   const double *__restrict__ weights, T *__restrict__ g, Seg sg)
+    k_ace_pairgrad_d(const double *__restrict__ pos, int n, Box b0,
+                     const int32_t *__restrict__ species, int cap, const int *__restrict__ nbr,
+                     const int *__restrict__ cnt, const int *__restrict__ S_idx,
+                     const int *__restrict__ S_local, const int *__restrict__ hdr,
+                     AceArgs<double> a, int wpb, const double *__restrict__ dEdA,
+                     const double *__restrict__ weights, double *__restrict__ g, Seg sg,
+                     const double *__restrict__ Kn)
 {
     const int nS = hdr[H_NS];
-    const int w = threadIdx.x >> 6;
-    const int lane = threadIdx.x & 63;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int s = blockIdx.x * wpb + w;
     if (s >= nS)
-        return;  // no barrier in this kernel
+        return;  // no block barrier in this kernel
     extern __shared__ __align__(16) char smem_raw[];
-    T *dAs = reinterpret_cast<T *>(smem_raw) + (size_t)w * a.KAt;
+    // per wave: the dE/dA row (KAt is a multiple of four), then the pair list
+    double *dAs = reinterpret_cast<double *>(smem_raw) + (size_t)w * (a.KAt + ((cap + 3) & ~3) / 2);
+    int *pl = reinterpret_cast<int *>(dAs + a.KAt);
     const int i = S_idx[s];
     const Box b = seg_box<SEG, true>(b0, sg, i);
-    T wgt = weights ? T(weights[i]) : T(1);
+    const double wgt = weights ? weights[i] : 1.0;
     for (int e = lane; e < a.KAt; e += 64)
         dAs[e] = dEdA[(size_t)s * a.KAt + e] * wgt;
-    // the wave reads back only its own slice: order the LDS writes before
-    // the reads of other lanes of the same wave
+    const int c = cnt[i];
+    const int *row = nbr + (size_t)i * cap;
+    double *gs = g + (size_t)s * cap * 3;
+    int nv = 0;
+    for (int base = 0; base < c; base += 64) {
+        const int slot = base + lane;
+        bool ok = false;
+        if (slot < c) {
+            const int j = row[slot];
+            if (S_local[j] >= 0) {
+                double d[3];
+                pair_disp_d(pos, n, i, j, b, d);
+                ok = norm2_d(d) < a.rc2;
+            }
+            if (!ok) {
+                gs[slot * 3 + 0] = 0.0;
+                gs[slot * 3 + 1] = 0.0;
+                gs[slot * 3 + 2] = 0.0;
+            }
+        }
+        const unsigned long long m = __ballot(ok);
+        if (ok)
+            pl[nv + __popcll(m & ((1ull << lane) - 1ull))] = slot;
+        nv += __popcll(m);
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    int c = cnt[i];
-    const int *row = nbr + (size_t)i * cap;
-    T *gs = g + (size_t)s * cap * 3;
-    for (int base = 0; base < c; base += 64) {
-        int slot = base + lane;
-        if (slot >= c)
-            continue;
-        int j = row[slot];
-        T gx = T(0), gy = T(0), gz = T(0);
-        if (S_local[j] >= 0) {
-            double d[3];
-            pair_disp_d(pos, n, i, j, b, d);
-            double r2 = norm2_d(d);
-            if (r2 < a.rc2) {
-                double rd = sqrt(r2);
-                double ird = 1.0 / rd;
-                T r = T(rd);
-                T ux = T(d[0] * ird), uy = T(d[1] * ird), uz = T(d[2] * ird);
-                T R[kMaxNrad], dR[kMaxNrad];
-                radial<T>(a.nrad, r, a.rc, R, dR);
-                const T *col = dAs + sp_clamp(species[j], a.ns) * a.nrad;
-                T rad = T(0), vx = T(0), vy = T(0), vz = T(0);
-                const int nchp = a.nchp, nrad = a.nrad;
-                ylm_stream<T>(a.lmax, ux, uy, uz, a.K, [&](int lm, T Y, T yx, T yy, T yz) {
-                    T sR = T(0), sD = T(0);
-                    const T *cl = col + lm * nchp;
+    for (int k = lane; k < nv; k += 64) {
+        const int slot = pl[k];
+        const int j = row[slot];
+        double d[3];
+        pair_disp_d(pos, n, i, j, b, d);
+        const double r = sqrt(norm2_d(d)), ir = 1.0 / r;
+        const double ux = d[0] * ir, uy = d[1] * ir, uz = d[2] * ir;
+        double R[kMaxNrad], dR[kMaxNrad];
+        const int nrad = NR > 0 ? NR : a.nrad;
+        radial<double>(nrad, r, a.rc, R, dR);
+        const double *col = dAs + sp_clamp(species[j], a.ns) * nrad;
+        double rad = 0.0, vx = 0.0, vy = 0.0, vz = 0.0;
+        const int nchp = a.nchp;
+        ylm_fixed<LM>(ux, uy, uz, Kn, [&](int lm, bool, double Y, double yx, double yy, double yz) {
+            double sR = 0.0, sD = 0.0;
+            const double *cl = col + lm * nchp;
 #pragma unroll
-                    for (int k = 0; k < kMaxNrad; ++k)
-                        if (k < nrad) {
-                            T v = cl[k];
-                            sR += v * R[k];
-                            sD += v * dR[k];
-                        }
-                    rad += sD * Y;
-                    vx += sR * yx;
-                    vy += sR * yy;
-                    vz += sR * yz;
-                });
-                // grad of Y(d/|d|) w.r.t. d is (I - u u^T) grad_u Y / r
-                T ud = ux * vx + uy * vy + uz * vz;
-                T ir = T(ird);
-                gx = rad * ux + (vx - ux * ud) * ir;
-                gy = rad * uy + (vy - uy * ud) * ir;
-                gz = rad * uz + (vz - uz * ud) * ir;
-            }
-        }
-        gs[slot * 3 + 0] = gx;
-        gs[slot * 3 + 1] = gy;
-        gs[slot * 3 + 2] = gz;
+            for (int q = 0; q < (NR > 0 ? NR : kMaxNrad); ++q)
+                if (q < nrad) {
+                    const double v = cl[q];
+                    sR = fma_t(v, R[q], sR);
+                    sD = fma_t(v, dR[q], sD);
+                }
+            rad = fma_t(sD, Y, rad);
+            vx = fma_t(sR, yx, vx);
+            vy = fma_t(sR, yy, vy);
+            vz = fma_t(sR, yz, vz);
+        });
+        // grad of Y(d/|d|) w.r.t. d is (I - u u^T) grad_u Y / r
+        const double ud = ux * vx + uy * vy + uz * vz;
+        gs[slot * 3 + 0] = rad * ux + (vx - ux * ud) * ir;
+        gs[slot * 3 + 1] = rad * uy + (vy - uy * ud) * ir;
+        gs[slot * 3 + 2] = rad * uz + (vz - uz * ud) * ir;
     }
 }
 
-// The same pair adjoint in FP32 with two S atoms per wave (32 lanes each) for
+// The pair adjoint in FP32 with two S atoms per wave (32 lanes each) for
 // large systems: each half first lists its row's valid pairs (partner in S,
 // inside the cutoff) in LDS by ballot, then its 32 lanes take the listed
 // pairs 32 at a time, recomputing the geometry; invalid slots get a zero
 // gradient from their owner lane. At lmax 5 and 26 pairs in a row of 64 slots
 // this keeps about 80 % of the lanes on the harmonic work instead of 40 %.
-template <bool SEG>
+template <int LM, int NR, bool SEG>
 __global__ void __launch_bounds__(256)
     k_ace_pairgrad_h(const double *__restrict__ pos, int n, Box b0,
                      const int32_t *__restrict__ species, int cap, const int *__restrict__ nbr,
                      const int *__restrict__ cnt, const int *__restrict__ S_idx,
                      const int *__restrict__ S_local, const int *__restrict__ hdr,
                      AceArgs<float> a, const float *__restrict__ dEdA,
-                     const double *__restrict__ weights, float *__restrict__ g, Seg sg)
+                     const double *__restrict__ weights, float *__restrict__ g, Seg sg,
+                     const float *__restrict__ Kn)
 {
     const int nS = hdr[H_NS];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -721,11 +776,12 @@ __global__ void __launch_bounds__(256)
         const float r = float(rd);
         const float ux = float(d[0] * ird), uy = float(d[1] * ird), uz = float(d[2] * ird);
         float R[kMaxNrad], dR[kMaxNrad];
-        radial<float>(a.nrad, r, a.rc, R, dR);
-        const float *col = dA + sp_clamp(species[j], a.ns) * a.nrad;
+        const int nrad = NR > 0 ? NR : a.nrad;
+        radial<float>(nrad, r, a.rc, R, dR);
+        const float *col = dA + sp_clamp(species[j], a.ns) * nrad;
         float rad = 0.f, vx = 0.f, vy = 0.f, vz = 0.f;
-        const int nchp = a.nchp, nrad = a.nrad;
-        ylm_stream<float>(a.lmax, ux, uy, uz, a.K, [&](int lm, float Y, float yx, float yy, float yz) {
+        const int nchp = a.nchp;
+        ylm_fixed<LM>(ux, uy, uz, Kn, [&](int lm, bool low, float Y, float yx, float yy, float yz) {
             float sR = 0.f, sD = 0.f;
             const float *cl = col + lm * nchp;
 #pragma unroll
@@ -735,10 +791,7 @@ __global__ void __launch_bounds__(256)
                     sR += v * R[q];
                     sD += v * dR[q];
                 }
-            rad += sD * Y;
-            vx += sR * yx;
-            vy += sR * yy;
-            vz += sR * yz;
+            harmonic_adjoint(low, sR, sD, Y, yx, yy, yz, rad, vx, vy, vz);
         });
         const float ud = ux * vx + uy * vy + uz * vz;
         const float ir = float(ird);
@@ -784,10 +837,12 @@ extern void pb_ranges(const Ctx &c, int *lo, int *hi);
 typedef float f4v_t __attribute__((ext_vector_type(4)));
 
 // Geometry of one valid expensive pair, in the compacted order of the row.
-struct PairGeo {
-    float r, ux, uy, uz, ir;
+template <typename T>
+struct PairGeoT {
+    T r, ux, uy, uz, ir;
     int zj, slot, pad;
 };
+using PairGeo = PairGeoT<float>;
 static_assert(sizeof(PairGeo) == 32, "PairGeo is eight 4-byte words");
 
 // Valid pairs of centre i (partner in S, inside the cutoff) over the whole
@@ -795,11 +850,12 @@ static_assert(sizeof(PairGeo) == 32, "PairGeo is eight 4-byte words");
 // ballots give each valid pair its index in row order (pp[u], -1 if not
 // valid) and the function returns their number. Pairs whose index lies in
 // [64 rnd, 64 rnd + 64) leave their geometry in geo[index - 64 rnd].
+template <typename T>
 __device__ __forceinline__ int compact_pairs(const double *__restrict__ pos, int n, const Box &b,
                                              const int32_t *__restrict__ species, int ns,
                                              const int *__restrict__ row, int c,
                                              const int *__restrict__ S_local, int i, double rc2,
-                                             int lane, int rnd, PairGeo *geo, int (&pp)[4])
+                                             int lane, int rnd, PairGeoT<T> *geo, int (&pp)[4])
 {
     int nv = 0;
 #pragma unroll
@@ -825,12 +881,12 @@ __device__ __forceinline__ int compact_pairs(const double *__restrict__ pos, int
             pp[u] = p;
             if (p >= 64 * rnd && p < 64 * rnd + 64) {
                 const double rd = sqrt(r2), ird = 1.0 / rd;
-                PairGeo gq;
-                gq.r = float(rd);
-                gq.ux = float(d[0] * ird);
-                gq.uy = float(d[1] * ird);
-                gq.uz = float(d[2] * ird);
-                gq.ir = float(ird);
+                PairGeoT<T> gq;
+                gq.r = T(rd);
+                gq.ux = T(d[0] * ird);
+                gq.uy = T(d[1] * ird);
+                gq.uz = T(d[2] * ird);
+                gq.ir = T(ird);
                 gq.zj = sp_clamp(species[j], ns);
                 gq.slot = slot;
                 gq.pad = 0;
@@ -845,10 +901,11 @@ __device__ __forceinline__ int compact_pairs(const double *__restrict__ pos, int
 // Geometry of the pairs with compacted index in [64 rnd, 64 rnd + 64) for a
 // later round (rows with more than 64 valid pairs): recomputed from the
 // positions with the same operations.
+template <typename T>
 __device__ __forceinline__ void pairs_round(const double *__restrict__ pos, int n, const Box &b,
                                             const int32_t *__restrict__ species, int ns,
                                             const int *__restrict__ row, int i, int lane, int rnd,
-                                            const int (&pp)[4], PairGeo *geo)
+                                            const int (&pp)[4], PairGeoT<T> *geo)
 {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -860,12 +917,12 @@ __device__ __forceinline__ void pairs_round(const double *__restrict__ pos, int 
             pair_disp_d(pos, n, i, j, b, d);
             const double r2 = norm2_d(d);
             const double rd = sqrt(r2), ird = 1.0 / rd;
-            PairGeo gq;
-            gq.r = float(rd);
-            gq.ux = float(d[0] * ird);
-            gq.uy = float(d[1] * ird);
-            gq.uz = float(d[2] * ird);
-            gq.ir = float(ird);
+            PairGeoT<T> gq;
+            gq.r = T(rd);
+            gq.ux = T(d[0] * ird);
+            gq.uy = T(d[1] * ird);
+            gq.uz = T(d[2] * ird);
+            gq.ir = T(ird);
             gq.zj = sp_clamp(species[j], ns);
             gq.slot = slot;
             gq.pad = 0;
@@ -886,14 +943,16 @@ __device__ __forceinline__ void wave_sync_ace()
 // large systems (1M atoms, lmax 5: 10.58 against 10.82 ms per step), where
 // the whole-row form below is slower; small systems take the whole-row form
 // (8,193 atoms: 132.7 against 135.4 us per step).
-template <int MT, int NT, bool SEG>
+template <int MT, int LM, bool SEG>
 __global__ void __launch_bounds__(256)
     k_ace_basis_mfma_chunks(const double *__restrict__ pos, int n, Box b0,
                      const int32_t *__restrict__ species, int cap, const int *__restrict__ nbr,
                      const int *__restrict__ cnt, const int *__restrict__ S_idx,
                      const int *__restrict__ S_local, const int *__restrict__ hdr,
-                     AceArgs<float> a, int wpb, float *__restrict__ A, Seg sg)
+                     AceArgs<float> a, int wpb, float *__restrict__ A, Seg sg,
+                            const float *__restrict__ Kn)
 {
+    constexpr int NT = lm_tiles(LM);
     constexpr int RW = 16 * MT + 1, YW = 16 * NT + 1;
     const int nS = hdr[H_NS];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -951,8 +1010,7 @@ __global__ void __launch_bounds__(256)
                 if (k < nrad)
                     rr[zj * nrad + k] = R[k];
             float *yr = Yt + p * YW;
-            ylm_stream<float>(a.lmax, ux, uy, uz, a.K,
-                              [&](int lm, float Y, float, float, float) { yr[lm] = Y; });
+            ylm_fixed<LM>(ux, uy, uz, Kn, [&](int lm, bool, float Y, float, float, float) { yr[lm] = Y; });
             for (int lm = L2; lm < 16 * NT; ++lm)
                 yr[lm] = 0.f;
         }
@@ -999,7 +1057,7 @@ __global__ void __launch_bounds__(256)
         }
 }
 
-// Atomic basis on the matrix cores (FP32 potentials): one wave per S atom.
+// Atomic basis on the matrix cores (FP32 and FP64): one wave per S atom.
 // The valid pairs of the whole row (partner in S, inside the cutoff) are
 // compacted by ballot first, their geometry left in LDS; lane q then
 // evaluates the radial functions and harmonics of compacted pair q into
@@ -1010,14 +1068,16 @@ __global__ void __launch_bounds__(256)
 // pairs, 64 per round; rows hold about 40 valid pairs, so one round). Row
 // strides are odd so that the row writes of the 64 lanes and the tile reads
 // are free of bank conflicts.
-template <int MT, int NT, bool SEG>
+template <typename T, int MT, int LM, bool SEG>
 __global__ void __launch_bounds__(256)
     k_ace_basis_mfma(const double *__restrict__ pos, int n, Box b0,
                      const int32_t *__restrict__ species, int cap, const int *__restrict__ nbr,
                      const int *__restrict__ cnt, const int *__restrict__ S_idx,
                      const int *__restrict__ S_local, const int *__restrict__ hdr,
-                     AceArgs<float> a, int wpb, float *__restrict__ A, Seg sg)
+                     AceArgs<T> a, int wpb, T *__restrict__ A, Seg sg,
+                     const T *__restrict__ Kn)
 {
+    constexpr int NT = lm_tiles(LM);
     constexpr int RW = 16 * MT + 1, YW = 16 * NT + 1;
     const int nS = hdr[H_NS];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1025,22 +1085,23 @@ __global__ void __launch_bounds__(256)
     if (s >= nS)
         return;  // no barriers in this kernel
     extern __shared__ __align__(16) char smem_raw[];
-    // per wave: R rows [64][RW], Y rows [64][YW], then 64 PairGeo (8 floats each)
-    float *Rz = reinterpret_cast<float *>(smem_raw) + (size_t)w * (64 * (RW + YW) + 64 * 8);
-    float *Yt = Rz + 64 * RW;
+    // per wave: R rows [64][RW], Y rows [64][YW], then 64 PairGeo
+    T *Rz = reinterpret_cast<T *>(smem_raw + (size_t)w * (64 * (RW + YW) * sizeof(T) +
+                                                          64 * sizeof(PairGeoT<T>)));
+    T *Yt = Rz + 64 * RW;
     const int m16 = lane & 15, kg = lane >> 4;
     const int i = S_idx[s];
     const Box b = seg_box<SEG, true>(b0, sg, i);
     const int c = cnt[i];
     const int *row = nbr + (size_t)i * cap;
     const int nrad = a.nrad, nch = a.nchan, L2 = a.L2;
-    f4v_t acc[MT][NT];
+    typename Mfma<T>::v4 acc[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-            acc[mt][nt] = (f4v_t){0.f, 0.f, 0.f, 0.f};
-    PairGeo *geo = reinterpret_cast<PairGeo *>(Yt + 64 * YW);  // [64]
+            acc[mt][nt] = (typename Mfma<T>::v4){T(0), T(0), T(0), T(0)};
+    PairGeoT<T> *geo = reinterpret_cast<PairGeoT<T> *>(Yt + 64 * YW);  // [64]
     int pp[4];
     const int nv_all = compact_pairs(pos, n, b, species, a.ns, row, c, S_local, i, a.rc2, lane, 0,
                                      geo, pp);
@@ -1052,31 +1113,31 @@ __global__ void __launch_bounds__(256)
         const int nv4 = (nv + 3) & ~3;
         // lane q builds the rows of compacted pair q (rows nv..nv4-1 zero)
         if (lane < nv) {
-            const PairGeo gq = geo[lane];
-            float R[kMaxNrad], dR[kMaxNrad];
-            radial<float>(nrad, gq.r, a.rc, R, dR);
-            float *rr = Rz + lane * RW;
+            const PairGeoT<T> gq = geo[lane];
+            T R[kMaxNrad], dR[kMaxNrad];
+            radial<T>(nrad, gq.r, a.rc, R, dR);
+            T *rr = Rz + lane * RW;
             for (int ch = 0; ch < 16 * MT; ++ch)
-                rr[ch] = 0.f;
+                rr[ch] = T(0);
 #pragma unroll
             for (int k = 0; k < kMaxNrad; ++k)
                 if (k < nrad)
                     rr[gq.zj * nrad + k] = R[k];
-            float *yr = Yt + lane * YW;
-            ylm_stream<float>(a.lmax, gq.ux, gq.uy, gq.uz, a.K,
-                              [&](int lm, float Y, float, float, float) { yr[lm] = Y; });
+            T *yr = Yt + lane * YW;
+            ylm_fixed<LM>(gq.ux, gq.uy, gq.uz, Kn,
+                          [&](int lm, bool, T Y, T, T, T) { yr[lm] = Y; });
             for (int lm = L2; lm < 16 * NT; ++lm)
-                yr[lm] = 0.f;
+                yr[lm] = T(0);
         } else if (lane < nv4) {
             for (int ch = 0; ch < 16 * MT; ++ch)
-                Rz[lane * RW + ch] = 0.f;
+                Rz[lane * RW + ch] = T(0);
             for (int lm = 0; lm < 16 * NT; ++lm)
-                Yt[lane * YW + lm] = 0.f;
+                Yt[lane * YW + lm] = T(0);
         }
         wave_sync_ace();
         for (int k0 = 0; k0 < nv4; k0 += 4) {
             const int kr = k0 + kg;
-            float xa[MT], yb[NT];
+            T xa[MT], yb[NT];
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
                 xa[mt] = Rz[kr * RW + mt * 16 + m16];
@@ -1087,20 +1148,31 @@ __global__ void __launch_bounds__(256)
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[mt], yb[nt], acc[mt][nt], 0, 0, 0);
+                    acc[mt][nt] = Mfma<T>::op(xa[mt], yb[nt], acc[mt][nt]);
         }
         wave_sync_ace();
     }
-    // lane holds A[ch = 16 mt + 4 kg + v][lm = 16 nt + m16]: four consecutive
-    // channels of one lm, stored as one 16-byte write (padded channels are 0)
-    float *As = A + (size_t)s * a.KAt;
+    // FP32: lane holds A[ch = 16 mt + 4 kg + v][lm = 16 nt + m16], four
+    // consecutive channels of one lm, stored as one 16-byte write; FP64: ch =
+    // 16 mt + 4 v + kg (padded channels are 0)
+    T *As = A + (size_t)s * a.KAt;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const int lm = nt * 16 + m16, ch0 = mt * 16 + 4 * kg;
-            if (lm < L2 && ch0 < a.nchp)
-                *reinterpret_cast<f4v_t *>(As + lm * a.nchp + ch0) = acc[mt][nt];
+            const int lm = nt * 16 + m16;
+            if constexpr (sizeof(T) == 4) {
+                const int ch0 = mt * 16 + 4 * kg;
+                if (lm < L2 && ch0 < a.nchp)
+                    *reinterpret_cast<typename Mfma<T>::v4 *>(As + lm * a.nchp + ch0) = acc[mt][nt];
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int ch = mt * 16 + 4 * v + kg;
+                    if (lm < L2 && ch < a.nchp)
+                        As[lm * a.nchp + ch] = acc[mt][nt][v];
+                }
+            }
         }
 }
 
@@ -1124,15 +1196,17 @@ struct FinArgs {
 // channels); each pair's lane then contracts its rows with the harmonics and
 // their gradients, g = rad u + (v - u (u.v)) / r with rad = sum S_D Y and
 // v = sum S_R grad_u Y, and writes g to its list slot (0 for other slots).
-template <int MT, int NT, bool SEG>
+template <int MT, int LM, bool SEG>
 __global__ void __launch_bounds__(256)
     k_ace_pairgrad_mfma(const double *__restrict__ pos, int n, Box b0,
                         const int32_t *__restrict__ species, int cap, const int *__restrict__ nbr,
                         const int *__restrict__ cnt, const int *__restrict__ S_idx,
                         const int *__restrict__ S_local, const int *__restrict__ hdr,
                         AceArgs<float> a, int wpb, const float *__restrict__ dEdA,
-                        const double *__restrict__ weights, float *__restrict__ g, Seg sg)
+                        const double *__restrict__ weights, float *__restrict__ g, Seg sg,
+                        const float *__restrict__ Kn)
 {
+    constexpr int NT = lm_tiles(LM);
     constexpr int RW = 16 * MT + 1, YW = 16 * NT + 1;
     constexpr int PAIR = 64 * RW * 2 > 64 * YW * 2 ? 64 * RW * 2 : 64 * YW * 2;
     const int nS = hdr[H_NS];
@@ -1249,12 +1323,8 @@ __global__ void __launch_bounds__(256)
             const PairGeo gq = geo[lane];
             const float *srow = SR + lane * YW, *drow = SD + lane * YW;
             float rad = 0.f, vx = 0.f, vy = 0.f, vz = 0.f;
-            ylm_stream<float>(a.lmax, gq.ux, gq.uy, gq.uz, a.K, [&](int lm, float Y, float yx, float yy, float yz) {
-                const float sR = srow[lm], sD = drow[lm];
-                rad += sD * Y;
-                vx += sR * yx;
-                vy += sR * yy;
-                vz += sR * yz;
+            ylm_fixed<LM>(gq.ux, gq.uy, gq.uz, Kn, [&](int lm, bool low, float Y, float yx, float yy, float yz) {
+                harmonic_adjoint(low, srow[lm], drow[lm], Y, yx, yy, yz, rad, vx, vy, vz);
             });
             const float ud = gq.ux * vx + gq.uy * vy + gq.uz * vz;
             gs[gq.slot * 3 + 0] = rad * gq.ux + (vx - gq.ux * ud) * gq.ir;
@@ -1298,15 +1368,17 @@ struct PairWgLds {
     static_assert(4 * 64 * 4 <= P_ROWS, "partial sums fit the R rows");
 };
 
-template <int MT, int NT, bool SEG>
+template <int MT, int LM, bool SEG>
 __global__ void __launch_bounds__(256)
     k_ace_pairgrad_wg(const double *__restrict__ pos, int n, Box b0,
                       const int32_t *__restrict__ species, int cap, const int *__restrict__ nbr,
                       const int *__restrict__ cnt, const int *__restrict__ S_idx,
                       const int *__restrict__ S_local, const int *__restrict__ hdr,
                       AceArgs<float> a, const double *__restrict__ weights,
-                      float *__restrict__ g, Seg sg, FinArgs fa)
+                      float *__restrict__ g, Seg sg, FinArgs fa,
+                      const float *__restrict__ Kn)
 {
+    constexpr int NT = lm_tiles(LM);
     using LY = PairWgLds<MT, NT, SEG>;
     constexpr int RW = LY::RW, YW = LY::YW;
     const int nS = hdr[H_NS];
@@ -1452,7 +1524,7 @@ __global__ void __launch_bounds__(256)
     const int nv_all = *nvs;
 
     // this wave's share of the orders |m|
-    const int m_lo = w, m_hi = w < 3 ? w : a.lmax;
+    const int m_lo = w, m_hi = w < 3 ? w : LM;
     for (int rnd = 0; 64 * rnd < nv_all; ++rnd) {
         if (rnd > 0) {
             __syncthreads();  // every wave is done with the last round's geo and S rows
@@ -1516,17 +1588,13 @@ __global__ void __launch_bounds__(256)
         // ---- 4. this wave's orders for every pair of the round (lane = pair)
         {
             float rad = 0.f, vx = 0.f, vy = 0.f, vz = 0.f;
-            if (lane < nv && m_lo <= a.lmax) {
+            if (lane < nv && m_lo <= LM) {
                 const PairGeo gq = geo[lane];
                 const float *srow = SR + lane * YW, *drow = SD + lane * YW;
-                ylm_stream<float>(
-                    a.lmax, gq.ux, gq.uy, gq.uz, a.K,
-                    [&](int lm, float Y, float yx, float yy, float yz) {
-                        const float sR = srow[lm], sD = drow[lm];
-                        rad += sD * Y;
-                        vx += sR * yx;
-                        vy += sR * yy;
-                        vz += sR * yz;
+                ylm_fixed<LM>(
+                    gq.ux, gq.uy, gq.uz, Kn,
+                    [&](int lm, bool low, float Y, float yx, float yy, float yz) {
+                        harmonic_adjoint(low, srow[lm], drow[lm], Y, yx, yy, yz, rad, vx, vy, vz);
                     },
                     m_lo, m_hi);
             }
@@ -1560,10 +1628,10 @@ __global__ void __launch_bounds__(256)
     }
 }
 
-template <int MT, int NT>
+template <typename T, int MT, int NT>
 static size_t basis_mfma_lds()
 {
-    return (size_t)64 * (16 * MT + 1 + 16 * NT + 1) * sizeof(float) + 64 * sizeof(PairGeo);
+    return (size_t)64 * (16 * MT + 1 + 16 * NT + 1) * sizeof(T) + 64 * sizeof(PairGeoT<T>);
 }
 template <int MT, int NT>
 static size_t pairgrad_mfma_lds()
@@ -1582,44 +1650,46 @@ static int mfma_wpb(size_t per_wave)
     return wpb;
 }
 
-template <int MT, int NT>
+template <typename T, int MT, int LM>
 static void basis_mfma_launch(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, const Box &b,
-                              const double *pos, const int32_t *species, const AceArgs<float> &a)
+                              const double *pos, const int32_t *species, const AceArgs<T> &a)
 {
+    constexpr int NT = lm_tiles(LM);
     // a batched call keeps the whole-row form whatever its total size: the
     // two forms group the pairs differently (different rounding), and a
     // system must give the same bits alone and in any batch
+    if constexpr (sizeof(T) == 4)
     if (c.basis_chunks > 0 || (c.basis_chunks < 0 && L.n > 65536 && L.nseg == 0)) {
         const size_t per = (size_t)64 * (16 * MT + 1 + 16 * NT + 1) * sizeof(float);
         const int wpb = mfma_wpb(per);
-        auto kern = L.nseg > 0 ? k_ace_basis_mfma_chunks<MT, NT, true>
-                               : k_ace_basis_mfma_chunks<MT, NT, false>;
+        auto kern = L.nseg > 0 ? k_ace_basis_mfma_chunks<MT, LM, true>
+                               : k_ace_basis_mfma_chunks<MT, LM, false>;
         kern<<<(L.n + wpb - 1) / wpb, 64 * wpb, per * wpb, s>>>(
             pos, L.n, b, species, L.cap, at<int>(ws, L.nbr), at<int>(ws, L.cnt),
             at<int>(ws, L.S_idx), at<int>(ws, L.S_local), at<int>(ws, L.hdr), a, wpb,
-            at<float>(ws, L.A), seg_args(ws, L));
+            at<float>(ws, L.A), seg_args(ws, L), a.K);
         return;
     }
-    const size_t per = basis_mfma_lds<MT, NT>();
+    const size_t per = basis_mfma_lds<T, MT, NT>();
     const int wpb = mfma_wpb(per);
-    auto kern = L.nseg > 0 ? k_ace_basis_mfma<MT, NT, true> : k_ace_basis_mfma<MT, NT, false>;
+    auto kern = L.nseg > 0 ? k_ace_basis_mfma<T, MT, LM, true> : k_ace_basis_mfma<T, MT, LM, false>;
     kern<<<(L.n + wpb - 1) / wpb, 64 * wpb, per * wpb, s>>>(
         pos, L.n, b, species, L.cap, at<int>(ws, L.nbr), at<int>(ws, L.cnt), at<int>(ws, L.S_idx),
-        at<int>(ws, L.S_local), at<int>(ws, L.hdr), a, wpb, at<float>(ws, L.A), seg_args(ws, L));
+        at<int>(ws, L.S_local), at<int>(ws, L.hdr), a, wpb, at<T>(ws, L.A), seg_args(ws, L), a.K);
 }
 
-template <int MT, int NT>
+template <int MT, int LM>
 static void pairgrad_mfma_launch(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
                                  const Box &b, const double *pos, const int32_t *species,
                                  const double *weights, const AceArgs<float> &a)
 {
-    const size_t per = pairgrad_mfma_lds<MT, NT>();
+    const size_t per = pairgrad_mfma_lds<MT, lm_tiles(LM)>();
     const int wpb = mfma_wpb(per);
-    auto kern = L.nseg > 0 ? k_ace_pairgrad_mfma<MT, NT, true> : k_ace_pairgrad_mfma<MT, NT, false>;
+    auto kern = L.nseg > 0 ? k_ace_pairgrad_mfma<MT, LM, true> : k_ace_pairgrad_mfma<MT, LM, false>;
     kern<<<(L.n + wpb - 1) / wpb, 64 * wpb, per * wpb, s>>>(
         pos, L.n, b, species, L.cap, at<int>(ws, L.nbr), at<int>(ws, L.cnt), at<int>(ws, L.S_idx),
         at<int>(ws, L.S_local), at<int>(ws, L.hdr), a, wpb, at<float>(ws, L.dEdA), weights,
-        at<float>(ws, L.g), seg_args(ws, L));
+        at<float>(ws, L.g), seg_args(ws, L), a.K);
 }
 
 // The workgroup pair adjoint with the folded finalisation: (channel tiles,
@@ -1643,16 +1713,16 @@ static bool pair_wg_tiles(const Ctx &c, int &mt, int &nt)
     return tot >= 1 && tot <= u && c.m.L2 + 1 + ncol <= tblcap;
 }
 
-template <int MT, int NT>
+template <int MT, int LM>
 static void pairgrad_wg_launch(hipStream_t s, const WsLayout &L, const Box &b, const double *pos,
                                const int32_t *species, void *ws, const AceArgs<float> &a,
                                const double *weights, const FinArgs &fin)
 {
-    const size_t lds = (size_t)PairWgLds<MT, NT, false>::FLOATS * sizeof(float);
-    auto kern = L.nseg > 0 ? k_ace_pairgrad_wg<MT, NT, true> : k_ace_pairgrad_wg<MT, NT, false>;
+    const size_t lds = (size_t)PairWgLds<MT, lm_tiles(LM), false>::FLOATS * sizeof(float);
+    auto kern = L.nseg > 0 ? k_ace_pairgrad_wg<MT, LM, true> : k_ace_pairgrad_wg<MT, LM, false>;
     kern<<<L.n, 256, lds, s>>>(pos, L.n, b, species, L.cap, at<int>(ws, L.nbr), at<int>(ws, L.cnt),
                                at<int>(ws, L.S_idx), at<int>(ws, L.S_local), at<int>(ws, L.hdr), a,
-                               weights, at<float>(ws, L.g), seg_args(ws, L), fin);
+                               weights, at<float>(ws, L.g), seg_args(ws, L), fin, a.K);
 }
 
 // (channel tiles, lm tiles) of the matrix-core basis / adjoint kernels: 0 if
@@ -1701,26 +1771,29 @@ static DSumSel dsum_sel(const Ctx &c, const WsLayout &L, bool fp32)
 
 // Dispatch over (channel tiles, lm tiles); false if the model is outside the
 // instantiated range (then the VALU kernels run).
-template <bool PAIR>
+template <typename T, bool PAIR>
 static bool mfma_dispatch(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, const Box &b,
                           const double *pos, const int32_t *species, const double *weights)
 {
-    AceArgs<float> a = make_args<float>(c);
+    AceArgs<T> a = make_args<T>(c);
     int mt, nt;
     if (!mfma_tiles(c, PAIR, mt, nt))
         return false;
-#define O3_GO(M, N)                                                                    \
-    if (mt == M && nt == N) {                                                          \
-        if (PAIR)                                                                      \
-            pairgrad_mfma_launch<M, N>(s, c, ws, L, b, pos, species, weights, a);      \
-        else                                                                           \
-            basis_mfma_launch<M, N>(s, c, ws, L, b, pos, species, a);                  \
-        return true;                                                                   \
-    }
-    O3_GO(1, 1) O3_GO(1, 2) O3_GO(1, 3) O3_GO(1, 4)
-    O3_GO(2, 1) O3_GO(2, 2) O3_GO(2, 3) O3_GO(2, 4)
-#undef O3_GO
-    return false;
+    by_lmax(c.m.lmax, [&](auto lm) {
+        constexpr int LM = decltype(lm)::value;
+        auto go = [&](auto mtc) {
+            constexpr int MT = decltype(mtc)::value;
+            if constexpr (!PAIR)
+                basis_mfma_launch<T, MT, LM>(s, c, ws, L, b, pos, species, a);
+            else if constexpr (lm_tiles(LM) <= 2)  // mfma_tiles: two lm tiles at most
+                pairgrad_mfma_launch<MT, LM>(s, c, ws, L, b, pos, species, weights, a);
+        };
+        if (mt == 1)
+            go(std::integral_constant<int, 1>());
+        else
+            go(std::integral_constant<int, 2>());
+    });
+    return true;
 }
 
 template <typename T>
@@ -1838,31 +1911,47 @@ static void finalize_t(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
             c.m.dp_stride, at<T>(ws, L.A), Dpart, at<T>(ws, L.dEdA), e_exp);
 }
 
+// f(integral_constant<radial functions>) for the counts compiled into the
+// vector pair adjoints (0: a guard per radial function)
+template <typename F>
+static void by_nrad(int nrad, F &&f)
+{
+    switch (nrad) {
+    case 8: f(std::integral_constant<int, 8>()); break;
+    case 12: f(std::integral_constant<int, 12>()); break;
+    case 16: f(std::integral_constant<int, 16>()); break;
+    default: f(std::integral_constant<int, 0>()); break;
+    }
+}
+
+// The vector pair adjoints: FP32 with two atoms per wave, FP64 with one.
 template <typename T>
 static void pairgrad_t(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, const Box &b,
                        const double *pos, const int32_t *species, const double *weights)
 {
     AceArgs<T> a = make_args<T>(c);
-    int n = L.n;
-    if constexpr (sizeof(T) == 4) {
-        if (c.pair_half) {
-            // two atoms per wave, four waves per workgroup
-            const size_t sm = (size_t)4 * (2 * a.KAt + 2 * L.cap) * sizeof(float);
-            auto kern = L.nseg > 0 ? k_ace_pairgrad_h<true> : k_ace_pairgrad_h<false>;
-            kern<<<(n + 7) / 8, 256, sm, s>>>(
-                pos, n, b, species, L.cap, at<int>(ws, L.nbr), at<int>(ws, L.cnt),
-                at<int>(ws, L.S_idx), at<int>(ws, L.S_local), at<int>(ws, L.hdr), a,
-                at<float>(ws, L.dEdA), weights, at<float>(ws, L.g), seg_args(ws, L));
-            return;
-        }
-    }
-    const int wpb = 4;
-    size_t sm = (size_t)wpb * a.KAt * sizeof(T) + 16;
-    auto kern = L.nseg > 0 ? k_ace_pairgrad<T, true> : k_ace_pairgrad<T, false>;
-    kern<<<(n + wpb - 1) / wpb, 64 * wpb, sm, s>>>(
-        pos, n, b, species, L.cap, at<int>(ws, L.nbr), at<int>(ws, L.cnt), at<int>(ws, L.S_idx),
-        at<int>(ws, L.S_local), at<int>(ws, L.hdr), a, wpb, at<T>(ws, L.dEdA), weights,
-        at<T>(ws, L.g), seg_args(ws, L));
+    const int n = L.n;
+    by_lmax(a.lmax, [&](auto lm) {
+        by_nrad(a.nrad, [&](auto nr) {
+            constexpr int LM = decltype(lm)::value, NR = decltype(nr)::value;
+            if constexpr (sizeof(T) == 4) {
+                const size_t sm = (size_t)4 * (2 * a.KAt + 2 * L.cap) * sizeof(float);
+                auto kern = L.nseg > 0 ? k_ace_pairgrad_h<LM, NR, true> : k_ace_pairgrad_h<LM, NR, false>;
+                kern<<<(n + 7) / 8, 256, sm, s>>>(
+                    pos, n, b, species, L.cap, at<int>(ws, L.nbr), at<int>(ws, L.cnt),
+                    at<int>(ws, L.S_idx), at<int>(ws, L.S_local), at<int>(ws, L.hdr), a,
+                    at<float>(ws, L.dEdA), weights, at<float>(ws, L.g), seg_args(ws, L), a.K);
+            } else {
+                const int wpb = 4;
+                const size_t sm = (size_t)wpb * (a.KAt + ((L.cap + 3) & ~3) / 2) * sizeof(double);
+                auto kern = L.nseg > 0 ? k_ace_pairgrad_d<LM, NR, true> : k_ace_pairgrad_d<LM, NR, false>;
+                kern<<<(n + wpb - 1) / wpb, 64 * wpb, sm, s>>>(
+                    pos, n, b, species, L.cap, at<int>(ws, L.nbr), at<int>(ws, L.cnt),
+                    at<int>(ws, L.S_idx), at<int>(ws, L.S_local), at<int>(ws, L.hdr), a, wpb,
+                    at<double>(ws, L.dEdA), weights, at<double>(ws, L.g), seg_args(ws, L), a.K);
+            }
+        });
+    });
 }
 
 void launch_ace_basis(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, const Box &b,
@@ -1870,9 +1959,10 @@ void launch_ace_basis(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, 
 {
     if (L.n == 0)
         return;
-    if (c.prec == MLMIX_FP64)
-        basis_t<double>(s, c, ws, L, b, pos, species);
-    else if (!(c.basis_mfma && mfma_dispatch<false>(s, c, ws, L, b, pos, species, nullptr)))
+    if (c.prec == MLMIX_FP64) {
+        if (!(c.basis_mfma && mfma_dispatch<double, false>(s, c, ws, L, b, pos, species, nullptr)))
+            basis_t<double>(s, c, ws, L, b, pos, species);
+    } else if (!(c.basis_mfma && mfma_dispatch<float, false>(s, c, ws, L, b, pos, species, nullptr)))
         basis_t<float>(s, c, ws, L, b, pos, species);
 }
 
@@ -1926,14 +2016,18 @@ void launch_ace_pairgrad(hipStream_t s, const Ctx &c, void *ws, const WsLayout &
         const AceArgs<float> a = make_args<float>(c);
         int mt, nt;
         pair_wg_tiles(c, mt, nt);
-#define WG_GO(M, N)                                                        \
-    if (mt == M && nt == N)                                                \
-        pairgrad_wg_launch<M, N>(s, L, b, pos, species, ws, a, weights, fa);
-        WG_GO(1, 1) WG_GO(1, 2) WG_GO(1, 3) WG_GO(2, 1) WG_GO(2, 2) WG_GO(2, 3)
-#undef WG_GO
+        by_lmax(c.m.lmax, [&](auto lm) {
+            constexpr int LM = decltype(lm)::value;
+            if constexpr (lm_tiles(LM) <= 3) {  // pair_wg_tiles: three lm tiles at most
+                if (mt == 1)
+                    pairgrad_wg_launch<1, LM>(s, L, b, pos, species, ws, a, weights, fa);
+                else
+                    pairgrad_wg_launch<2, LM>(s, L, b, pos, species, ws, a, weights, fa);
+            }
+        });
     } else if (c.prec == MLMIX_FP64)
         pairgrad_t<double>(s, c, ws, L, b, pos, species, weights);
-    else if (!(c.basis_mfma && mfma_dispatch<true>(s, c, ws, L, b, pos, species, weights)))
+    else if (!(c.basis_mfma && mfma_dispatch<float, true>(s, c, ws, L, b, pos, species, weights)))
         pairgrad_t<float>(s, c, ws, L, b, pos, species, weights);
 }
 

@@ -122,4 +122,81 @@ __host__ __device__ inline void ylm_stream(int lmax, T x, T y, T z, const T *__r
     }
 }
 
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// The same stream for a compile-time lmax: the operations, their order and
+// their roundings are those that ylm_stream compiles to (so are the bits; the
+// fused products are written out, since folded constants would change the
+// compiler's choice), with no loop, switch or normalisation load between two
+// harmonics. K is read at constant offsets (uniform: batched scalar loads).
+// emit(lm, low, Y, grad Y) with low = (m <= 0).
+template <int LM, typename T, typename F>
+__device__ __forceinline__ void ylm_fixed(T x, T y, T z, const T *__restrict__ K, F &&emit,
+                                          int m_lo = 0, int m_hi = LM)
+{
+#pragma clang fp contract(off)
+    T Cm = T(1), Sm = T(0), Cp = T(0), Sp = T(0);
+    T dfm = T(1);
+#pragma unroll
+    for (int m = 0; m <= LM; ++m) {
+        if (m > m_hi)
+            return;
+        if (m > 0) {
+            T c = fma_t(x, Cm, -(y * Sm));
+            T s = fma_t(y, Cm, x * Sm);
+            Cp = Cm;
+            Sp = Sm;
+            Cm = c;
+            Sm = s;
+            dfm *= T(2 * m - 1);
+        }
+        if (m < m_lo)
+            continue;
+        T dfm1 = dfm * T(2 * m + 1);
+        T qa1 = T(0), qa2 = T(0), qb1 = T(0), qb2 = T(0);
+#pragma unroll
+        for (int l = m; l <= LM; ++l) {
+            T qa = (l == m) ? dfm
+                            : fma_t(qa1, T(2 * l - 1) * z, -(T(l + m - 1) * qa2)) * inv_small<T>(l - m);
+            T qb = (l == m) ? T(0)
+                            : (l == m + 1 ? dfm1
+                                          : fma_t(qb1, T(2 * l - 1) * z, -(T(l + m) * qb2)) *
+                                                inv_small<T>(l - m - 1));
+            const int base = l * l + l;
+            if (m == 0) {
+                T k0 = K[base];
+                emit(base, true, k0 * qa, T(0), T(0), k0 * qb);
+            } else {
+                T kp = K[base + m];
+                T kq = kp * qa;
+                T fm = T(m);
+                emit(base + m, false, kq * Cm, kq * fm * Cp, -kq * fm * Sp, kp * qb * Cm);
+                emit(base - m, true, kq * Sm, kq * fm * Sp, kq * fm * Cp, kp * qb * Sm);
+            }
+            qa2 = qa1;
+            qa1 = qa;
+            qb2 = qb1;
+            qb1 = qb;
+        }
+    }
+}
+
+// Adds one harmonic's share of a pair's adjoint: rad += sD Y, v += sR grad Y.
+// The z product of the orders m <= 0 is rounded before its sum (each order
+// pair's last sum; every other product is fused).
+template <typename T>
+__device__ __forceinline__ void harmonic_adjoint(bool low, T sR, T sD, T Y, T yx, T yy,
+                                                 T yz, T &rad, T &vx, T &vy, T &vz)
+{
+#pragma clang fp contract(off)
+    rad = fma_t(sD, Y, rad);
+    vx = fma_t(sR, yx, vx);
+    vy = fma_t(sR, yy, vy);
+    if (low)
+        vz = vz + sR * yz;
+    else
+        vz = fma_t(sR, yz, vz);
+}
+
 }  // namespace mlmix
