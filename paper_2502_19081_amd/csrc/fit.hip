@@ -5,13 +5,13 @@
 // configuration's energy and forces are A u for a design matrix A. Three
 // kernels build and solve the fit:
 //  - k_fit_design: one wavefront per atom i produces the derivatives of F_i
-//    (three rows) and of the site energy E_i by every parameter. Lane t owns
-//    parameter columns t and t + 64. Interactions are produced 64 at a time
-//    (one per lane) as records in LDS and then consumed by every lane for its
-//    own columns, so each output element is a sum in a fixed order (no
-//    atomics). F_i collects the pairs of i, the triplets centred on i, and the
-//    triplets centred on a neighbour j in which i is a leg (the other leg
-//    from j's 3-body list, built beforehand by k_fit_list3).
+//    (three rows) and of the site energy E_i by every parameter as small dense
+//    products over i's interactions, on the FP64 matrix cores. Interactions
+//    are produced up to 64 at a time (one per lane) as records in LDS, then
+//    contracted four at a time, so each output element is a sum in a fixed
+//    order (no atomics). F_i collects the pairs of i, the triplets centred on
+//    i, and the triplets centred on a neighbour j in which i is a leg (the
+//    other leg from j's 3-body list, built beforehand by k_fit_list3).
 //  - k_fit_gram_partial / k_fit_gram_reduce: G = A^T diag(w) A and
 //    b = A^T diag(w) y. Each workgroup stages 32 rows at a time in LDS and
 //    every thread accumulates 4 x 4 blocks of the upper triangle; partials of
@@ -24,85 +24,66 @@
 //    is at most alpha, then interval bisection until it is within tol of
 //    alpha. Every loop has a fixed bound.
 // Everything is FP64 whatever the context's force precision.
+#include <algorithm>
+#include <type_traits>
+
 #include "internal.h"
 
 namespace mlmix {
 
 constexpr int kFitWave = 64;
-constexpr int kFitColsPerLane = 2;  // columns per lane: kFitMaxParams <= 128
+
+// Orders one wavefront's LDS writes before its later LDS reads.
+__device__ __forceinline__ void fit_wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // ---------------------------------------------------------------- B-splines
 
 // The four non-zero clamped uniform cubic B-splines at x (0 <= x < top) and
 // their derivatives, by the Cox-de Boor triangle on the span holding x. The
 // recursion runs in knot units u = x / h (B-splines do not change when x and
-// the knots are scaled together), where every knot difference is a small
-// integer, so no division is left; ih = 1/h = (npts - 1)/top. The functions
-// are B_first .. B_first+3.
-__device__ __forceinline__ int fit_k(int i, int npts)
-{
-    const int k = i - 3;
-    return k < 0 ? 0 : (k > npts - 1 ? npts - 1 : k);
-}
-
-__device__ __forceinline__ double fit_inv_small(int m)
-{
-    // 1/m for the knot-difference counts 1..3 that occur (0 never divides)
-    return m == 1 ? 1.0 : (m == 2 ? 0.5 : 1.0 / 3.0);
-}
-
-__device__ void fit_bspline(double x, int npts, double ih, int &first, double N[4], double dN[4])
+// the knots are scaled together), where the knot differences are 1, 2 or 3 and
+// those of the derivative are the last stage's, so no division is left; ih =
+// 1/h = (npts - 1)/top. The functions are B_first .. B_first+3.
+__device__ __forceinline__ void fit_bspline(double x, int npts, double ih, int &first, double N[4],
+                                            double dN[4])
 {
     const double u = x * ih;
-    int sp = (int)floor(u);
-    sp = sp < 0 ? 0 : (sp > npts - 2 ? npts - 2 : sp);
-    const int mu = sp + 3;
-    double B[4] = {1.0, 0.0, 0.0, 0.0}, B2[3] = {0.0, 0.0, 0.0};
-    double left[4], right[4];
-#pragma unroll
-    for (int j = 1; j <= 3; ++j) {
-        left[j] = u - (double)fit_k(mu + 1 - j, npts);
-        right[j] = (double)fit_k(mu + j, npts) - u;
-        double saved = 0.0;
-#pragma unroll
-        for (int r = 0; r < j; ++r) {
-            const int m = fit_k(mu + r + 1, npts) - fit_k(mu + 1 - j + r, npts);
-            const double tmp = B[r] * fit_inv_small(m);
-            B[r] = saved + right[r + 1] * tmp;
-            saved = left[j - r] * tmp;
-        }
-        B[j] = saved;
-        if (j == 2) {
-            B2[0] = B[0];
-            B2[1] = B[1];
-            B2[2] = B[2];
-        }
-    }
-    // dB_k/du = 3 (B2_k / (K_k+3 - K_k) - B2_k+1 / (K_k+4 - K_k+1)), with the
-    // degree-2 functions B2_{mu-2..mu} non-zero; d/dx = ih d/du
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int k = mu - 3 + r;
-        const double a = r >= 1 ? B2[r - 1] * fit_inv_small(fit_k(k + 3, npts) - fit_k(k, npts)) : 0.0;
-        const double b = r <= 2 ? B2[r] * fit_inv_small(fit_k(k + 4, npts) - fit_k(k + 1, npts)) : 0.0;
-        N[r] = B[r];
-        dN[r] = 3.0 * ih * (a - b);
-    }
-    first = sp;
+    const double k0 = fmin(fmax(floor(u), 0.0), (double)(npts - 2)), top = (double)(npts - 1);
+    // knots K_mu-2 .. K_mu+3 (K_mu = k0, clamped at both ends)
+    const double km2 = fmax(k0 - 2.0, 0.0), km1 = fmax(k0 - 1.0, 0.0), k1 = k0 + 1.0;
+    const double k2 = fmin(k0 + 2.0, top), k3 = fmin(k0 + 3.0, top);
+    const double l1 = u - k0, l2 = u - km1, l3 = u - km2, r1 = k1 - u, r2 = k2 - u, r3 = k3 - u;
+    auto inv2 = [](double d) { return 1.5 - 0.5 * d; };  // d = 1, 2
+    auto inv3 = [](double d) { return d == 3.0 ? 1.0 / 3.0 : 1.5 - 0.5 * d; };
+    // degree 1: r1, l1 (the span is one knot wide); degree 2
+    const double a0 = r1 * inv2(k1 - km1), a1 = l1 * inv2(k2 - k0);
+    const double b0 = r1 * a0, b1 = l2 * a0 + r2 * a1, b2 = l1 * a1;
+    // degree 3
+    const double c0 = b0 * inv3(k1 - km2), c1 = b1 * inv3(k2 - km1), c2 = b2 * inv3(k3 - k0);
+    N[0] = r1 * c0;
+    N[1] = l3 * c0 + r2 * c1;
+    N[2] = l2 * c1 + r3 * c2;
+    N[3] = l1 * c2;
+    const double h3 = 3.0 * ih;
+    dN[0] = h3 * -c0;
+    dN[1] = h3 * (c0 - c1);
+    dN[2] = h3 * (c1 - c2);
+    dN[3] = h3 * c2;
+    first = (int)k0;
 }
 
-__device__ __forceinline__ double fit_win(const double *v, int first, int idx)
-{
-    const unsigned o = (unsigned)(idx - first);
-    return o < 4u ? v[o] : 0.0;
-}
-
-__device__ __forceinline__ double fit_disp(const double *__restrict__ pos, int n, int i, int j,
-                                           const Box &b, double d[3])
+// d = xj - xi (minimum image), returns |d|^2
+__device__ __forceinline__ double fit_fold(const double xi[3], const double xj[3], const Box &b,
+                                           double d[3])
 {
 #pragma clang fp contract(off)
     for (int k = 0; k < 3; ++k) {
-        double dx = pos[k * n + j] - pos[k * n + i];
+        double dx = xj[k] - xi[k];
         if (b.per[k]) {
             const double hh = 0.5 * b.L[k];
             dx = dx > hh ? dx - b.L[k] : (dx < -hh ? dx + b.L[k] : dx);
@@ -115,6 +96,14 @@ __device__ __forceinline__ double fit_disp(const double *__restrict__ pos, int n
     return r2;
 }
 
+__device__ __forceinline__ double fit_disp(const double *__restrict__ pos, int n, int i, int j,
+                                           const Box &b, double d[3])
+{
+    const double xi[3] = {pos[i], pos[n + i], pos[2 * n + i]};
+    const double xj[3] = {pos[j], pos[n + j], pos[2 * n + j]};
+    return fit_fold(xi, xj, b, d);
+}
+
 // ------------------------------------------------------------ design rows
 
 struct FitShape {
@@ -123,48 +112,37 @@ struct FitShape {
     double ih2, ih3, ih3c;         // knots per A: 2-body, 3-body legs, third side
 };
 
-// Column k decoded: kind 2 (species pair a <= b, spline p) or 3 (centre
-// species a, leg pair index p of (p1 <= p2), third side s); kind 0 = none.
+// 2-body column k decoded: species pair a <= b, spline p.
 struct FitCol {
-    int kind, a, b, p, s;
+    int a, b, p;
 };
 
-__device__ FitCol fit_decode(const FitShape &sh, int k)
+__device__ __forceinline__ FitCol fit_decode2(const FitShape &sh, int k)
 {
-    FitCol c{0, 0, 0, 0, 0};
-    if (k >= sh.nd)
+    FitCol c{-1, -1, 0};
+    if (k >= sh.n2cols)
         return c;
     const int nf2 = sh.nk2 - 1;  // nb2 - 3
-    if (k < sh.n2cols) {
-        int pair = k / nf2;
-        c.kind = 2;
-        c.p = k - pair * nf2;
-        for (int za = 0; za < sh.ns; ++za) {
-            const int row = sh.ns - za;
-            if (pair < row) {
-                c.a = za;
-                c.b = za + pair;
-                break;
-            }
-            pair -= row;
+    int pair = k / nf2;
+    c.p = k - pair * nf2;
+    for (int za = 0; za < sh.ns; ++za) {
+        const int row = sh.ns - za;
+        if (pair < row) {
+            c.a = za;
+            c.b = za + pair;
+            break;
         }
-        return c;
+        pair -= row;
     }
-    const int nb3 = sh.nk3 + 2, nf3 = sh.nk3 - 1;
-    const int per_z = nf3 * (nf3 + 1) / 2 * nb3;
-    int r = k - sh.n2cols;
-    c.kind = 3;
-    c.a = r / per_z;
-    r -= c.a * per_z;
-    c.p = r / nb3;
-    c.s = r - c.p * nb3;
     return c;
 }
 
-// Entry of the list of i's neighbours inside the 3-body cutoff.
+// Entry of the list of i's neighbours inside the 3-body cutoff, the leg
+// functions that are fitted written out densely (at most four: FitDims), with
+// a zero that selections of no function read.
 struct FitLeg {
-    int j, z, f;
-    double d[3], ir, B[4], dB[4];  // d = x_j - x_i, ir = 1/|d|
+    int j, z;
+    double d[3], u[3], B[5], dB[5];  // d = x_j - x_i, u = d / |d|
 };
 
 // One configuration of a batched design launch (everything per workspace).
@@ -190,40 +168,71 @@ static_assert(sizeof(FitBatch) + 64 <= 4096, "design launch arguments exceed 4 K
 
 __device__ __forceinline__ int fit_cfg_of(const FitBatch &B, int b)
 {
-    int c = 0;
-    while (c + 1 < B.ncfg && B.atom0[c + 1] <= b)
-        ++c;
-    return c;
+    // one bound per lane instead of a chain of dependent reads (kFitBatch <= 64)
+    const int l = threadIdx.x & 63;
+    return __popcll(__ballot(l + 1 < B.ncfg && B.atom0[min(l + 1, kFitBatch)] <= b));
 }
 
-constexpr int kFitRec = 16;   // records per batch
+constexpr int kFitRec = 64;   // triplet records per batch
 constexpr int kFitLegs = 32;  // 3-body neighbours per atom in the design kernel
 
-// Dense records in dynamic LDS, record index fastest:
-//   pairs:    B[nf2][R], dB[nf2][R] (the 2-body basis and its derivative)
-//   triplets: P, Pa, Pb [npq][R] (leg products symmetrised over p1 <= p2 and
-//             their derivatives by leg a and leg b), C, dC [nb3][R] (third side)
-//   then v1, v2 [3][R] (force directions), z [R], centre [R] (ints).
-__host__ __device__ inline int fit_dense(int nk2, int nk3)
+// Sizes of the 3-body part for NF3 fitted functions per leg (knots - 1) and CG
+// groups of four columns (species x third-side function). The limit of
+// kFitMaxParams columns leaves NF3 = 3 (one or two species) and 4 (one): five
+// functions alone would take 15 x 8 = 120 columns.
+template <int NF3, int CG>
+struct FitDims {
+    static constexpr int NPQ = NF3 * (NF3 + 1) / 2, NB3 = NF3 + 3;
+    // record of a leg triplet: the other leg's functions (four), the weights
+    // 1 and the third side's direction, the third-side functions and their
+    // derivatives; of a centred one: the third-side functions. Odd strides:
+    // neither the lanes' row writes nor the column reads conflict.
+    static constexpr int B = 0, W = 4, C = 8, E = C + NB3, RS = (E + NB3) | 1, RC = NB3 | 1;
+};
+__host__ __device__ inline int fit_pair_stride(int nf2) { return (2 * nf2 + 3) | 1; }
+
+// Value of the lane with the same lane / 16 and lane % 4 in block BLK of the
+// four blocks (lane / 4 % 4): a block of a 4x4x4 result as the right operand of
+// another 4x4x4 step, for all of its blocks.
+template <int BLK>
+__device__ __forceinline__ double fit_from_block(double v)
 {
-    const int nf2 = nk2 - 1;
-    const int nf3 = nk3 > 0 ? nk3 - 1 : 0;
-    const int npq = nf3 * (nf3 + 1) / 2;
-    const int t3 = nk3 > 0 ? 3 * npq + 2 * (nk3 + 2) : 0;
-    return 2 * nf2 > t3 ? 2 * nf2 : t3;
+    constexpr int pat = (4 * BLK) << 5 | 0x13;  // swizzle: keep lane bits 0, 1, 4; set the block
+    union {
+        double d;
+        int w[2];
+    } x{v};
+    x.w[0] = __builtin_amdgcn_ds_swizzle(x.w[0], pat);
+    x.w[1] = __builtin_amdgcn_ds_swizzle(x.w[1], pat);
+    return x.d;
 }
 
-size_t fit_design_lds(int nk2, int nk3)
+// Design rows of one atom per wavefront, as small dense products on the FP64
+// matrix cores in 4x4x4 steps of four blocks (16 cycles; the dimensions here
+// are about 4 and 7, where a 16x16x4 step would be mostly padding).
+// 2-body: 4 rows (components, energy) x 16 columns per step over the pairs.
+// 3-body, leg pair (p1, p2), third side s, per 3-body neighbour j of i with leg
+// functions a_j and direction u_j (b_jk: the other leg's functions):
+//   centred on i:  T[p][s]    = sum_k b_ik[p] C_jk[s]
+//                  E  += a_j T / 2,  F_q += u_jq a'_j T    (symmetrised over p1, p2)
+//   centred on j:  T[p][s]    = sum_k b_jk[p] C_ik[s],
+//                  T_q[p][s]  = sum_k b_jk[p] w_ikq C'_ik[s]
+//                  F_q += u_jq a'_j T + a_j T_q
+// so the sums over the records have four functions p as rows (the four blocks:
+// T and T_q, or four column groups of T), and the leg pairs appear once per j.
+// Bound by the FP64 vector work of building the records (splines, square
+// roots, reciprocals), which all 64 lanes share, and its latency.
+// 41,000 atoms, 81 columns: 3,053 -> 689 us.
+template <int NF3, int CG>
+__global__ void __launch_bounds__(kFitWave) k_fit_design(FitBatch Bt, FitShape sh, int rb2)
 {
-    return (size_t)(fit_dense(nk2, nk3) + 6) * kFitRec * sizeof(double) + 2 * kFitRec * sizeof(int);
-}
-
-__global__ void __launch_bounds__(kFitWave) k_fit_design(FitBatch Bt, FitShape sh)
-{
-    extern __shared__ double smem[];
-    __shared__ FitLeg leg[kFitLegs];
+    using FD = FitDims<NF3, CG>;
+    constexpr int NPQ = FD::NPQ, NB3 = FD::NB3, RS = FD::RS;
+    constexpr bool three = NF3 > 0;
+    extern __shared__ double rec[];
+    __shared__ FitLeg leg[three ? kFitLegs : 1];
     __shared__ int legpre[kFitLegs + 1];
-    __shared__ int nleg;
+    __shared__ int rz[kFitWave];
     const int cfg = fit_cfg_of(Bt, blockIdx.x);
     const FitCfgDev &Cf = Bt.c[cfg];
     const int n = Cf.n, cap = Cf.cap, ld = Bt.ld;
@@ -240,256 +249,401 @@ __global__ void __launch_bounds__(kFitWave) k_fit_design(FitBatch Bt, FitShape s
     const int i = blockIdx.x - Bt.atom0[cfg];
     const int lane = threadIdx.x;
     if (i >= n)
-        return;
-    constexpr int R = kFitRec;
-    const int nf2 = sh.nk2 - 1;
-    const bool three = sh.nk3 > 1;
-    const int nb3 = sh.nk3 + 2, nf3 = three ? sh.nk3 - 1 : 0;
-    const int npq = nf3 * (nf3 + 1) / 2;
-    const int dense = fit_dense(sh.nk2, sh.nk3);
-    double *D = smem;
-    double *V = smem + (size_t)dense * R;
-    int *RZ = reinterpret_cast<int *>(V + 6 * R);
-    int *RC = RZ + R;
-    double *P = D, *Pa = D + npq * R, *Pb = D + 2 * npq * R;
-    double *C = D + 3 * npq * R, *dC = C + nb3 * R;
-
+        return;  // uniform: one wavefront per workgroup
+    const int kg = lane >> 4, l16 = lane & 15;  // inner index of a step; row or column
+    const int nf2 = sh.nk2 - 1, rs2 = fit_pair_stride(nf2);
     const int zi = sp_clamp(species[i], sh.ns);
-    FitCol col[kFitColsPerLane];
-    double e[kFitColsPerLane], f[kFitColsPerLane][3];
-    for (int m = 0; m < kFitColsPerLane; ++m) {
-        col[m] = fit_decode(sh, lane + kFitWave * m);
-        e[m] = 0.0;
-        f[m][0] = f[m][1] = f[m][2] = 0.0;
-    }
     const double rc2sq = sh.rc2 * sh.rc2, rc3sq = sh.rc3 * sh.rc3;
     const int ci = cnt[i] < cap ? cnt[i] : cap;
-    if (lane == 0)
-        nleg = 0;
-    __syncthreads();
 
-    // 1. pairs of i (2-body columns), and the list of its 3-body legs
-    for (int base = 0; base < ci; base += R) {
+    // ---- 1. pairs of i (2-body columns), and the list of its 3-body legs
+    constexpr int T2 = (kFitMaxParams + 15) / 16;
+    const int nt2 = (sh.n2cols + 15) / 16;
+    double acc2[T2];
+    int need[T2], col2[T2];  // this lane's column 16 t + l16: partner species, spline
+#pragma unroll
+    for (int t = 0; t < T2; ++t) {
+        acc2[t] = 0.0;
+        need[t] = -2;
+        col2[t] = 0;
+        if (t < nt2) {
+            const FitCol c = fit_decode2(sh, 16 * t + l16);
+            need[t] = c.a == zi ? c.b : (c.b == zi ? c.a : -2);
+            col2[t] = c.p;
+        }
+    }
+    int m = 0;  // legs
+    for (int base = 0; base < ci; base += rb2) {
         const int slot = base + lane;
-        bool in3 = false;
+        bool in2 = false, in3 = false;
         double d[3] = {0.0, 0.0, 0.0}, r2 = 0.0;
         int j = -1;
-        if (lane < R) {
-            RZ[lane] = -1;
-            if (slot < ci) {
-                j = nbr[(size_t)i * cap + slot];
-                if (j >= 0 && j < n) {
-                    r2 = fit_disp(pos, n, i, j, box, d);
-                    const double r = sqrt(r2);
-                    if (r2 < rc2sq) {
-                        int fb;
-                        double Bw[4], dBw[4];
-                        fit_bspline(r, sh.nk2, sh.ih2, fb, Bw, dBw);
-                        RZ[lane] = sp_clamp(species[j], sh.ns);
-                        for (int q = 0; q < nf2; ++q) {
-                            const unsigned o = (unsigned)(q - fb);
-                            D[q * R + lane] = o < 4u ? Bw[o] : 0.0;
-                            D[(nf2 + q) * R + lane] = o < 4u ? dBw[o] : 0.0;
-                        }
-                        for (int k = 0; k < 3; ++k)
-                            V[k * R + lane] = d[k] / r;
-                    }
-                    in3 = three && r2 < rc3sq;
+        if (lane < rb2 && slot < ci) {
+            j = nbr[(size_t)i * cap + slot];
+            if (j >= 0 && j < n) {
+                r2 = fit_disp(pos, n, i, j, box, d);
+                in2 = r2 < rc2sq;
+                in3 = three && r2 < rc3sq;
+            }
+        }
+        const unsigned long long m2 = __ballot(in2), m3 = __ballot(in3);
+        const int nv = __popcll(m2), nv4 = (nv + 3) & ~3;
+        const double r = sqrt(r2);
+        if (in2) {
+            const int at = __popcll(m2 & ((1ull << lane) - 1ull));
+            double *q = rec + at * rs2;
+            int fb;
+            double Bw[4], dBw[4];
+            fit_bspline(r, sh.nk2, sh.ih2, fb, Bw, dBw);
+            for (int k = 0; k < 2 * nf2; ++k)
+                q[k] = 0.0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (fb + k < nf2) {
+                    q[fb + k] = Bw[k];
+                    q[nf2 + fb + k] = dBw[k];
                 }
-            }
+            const double ir = 1.0 / r;
+            for (int k = 0; k < 3; ++k)
+                q[2 * nf2 + k] = d[k] * ir;
+            rz[at] = sp_clamp(species[j], sh.ns);
         }
-        const unsigned long long m3 = __ballot(in3);
-        const int pos3 = nleg + __popcll(m3 & ((1ull << lane) - 1ull));
-        if (in3) {
-            if (pos3 < kFitLegs) {
-                FitLeg &G = leg[pos3];
-                const double r = sqrt(r2);
-                G.j = j;
-                G.z = sp_clamp(species[j], sh.ns);
-                G.ir = 1.0 / r;
-                for (int k = 0; k < 3; ++k)
-                    G.d[k] = d[k];
-                fit_bspline(r, sh.nk3, sh.ih3, G.f, G.B, G.dB);
-            } else {
-                atomicOr(&hdr[H_STATUS], MLMIX_STATUS_TRIPLET_OVERFLOW);
-            }
+        if (lane >= nv && lane < nv4) {  // rows that pad the inner dimension
+            for (int k = 0; k < rs2; ++k)
+                rec[lane * rs2 + k] = 0.0;
+            rz[lane] = -1;
         }
-        __syncthreads();
-        const int nrec = ci - base < R ? ci - base : R;
-        for (int t = 0; t < nrec; ++t) {
-            const int zj = RZ[t];
-            if (zj < 0)
-                continue;
-            const int lo = zj < zi ? zj : zi, hi = zj < zi ? zi : zj;
-            for (int m = 0; m < kFitColsPerLane; ++m) {
-                const FitCol &c = col[m];
-                if (c.kind != 2 || c.a != lo || c.b != hi)
-                    continue;
-                const double bv = D[c.p * R + t], dv = D[(nf2 + c.p) * R + t];
-                e[m] += 0.5 * bv;
-                for (int k = 0; k < 3; ++k)
-                    f[m][k] += dv * V[k * R + t];
-            }
-        }
-        if (lane == 0) {
-            const int tot = nleg + __popcll(m3);
-            nleg = tot < kFitLegs ? tot : kFitLegs;
-        }
-        __syncthreads();
-    }
-    const int m = nleg;
-
-    // dense leg products of one triplet record (lane t < R): legs a and b
-    // (windows fa/A/dA and fb/Bv/dBv), third side (fs/Cw/dCw)
-    auto put = [&](int t, int fa, const double *A, const double *dA, int fb, const double *Bv,
-                   const double *dBv, int fs, const double *Cw, const double *dCw, bool centre) {
-        int idx = 0;
-        for (int p1 = 0; p1 < nf3; ++p1) {
-            const unsigned o1a = (unsigned)(p1 - fa), o1b = (unsigned)(p1 - fb);
-            const double a1 = o1a < 4u ? A[o1a] : 0.0, da1 = o1a < 4u ? dA[o1a] : 0.0;
-            const double b1 = o1b < 4u ? Bv[o1b] : 0.0, db1 = o1b < 4u ? dBv[o1b] : 0.0;
-            for (int p2 = p1; p2 < nf3; ++p2, ++idx) {
-                const unsigned o2a = (unsigned)(p2 - fa), o2b = (unsigned)(p2 - fb);
-                const double a2 = o2a < 4u ? A[o2a] : 0.0, da2 = o2a < 4u ? dA[o2a] : 0.0;
-                const double b2 = o2b < 4u ? Bv[o2b] : 0.0, db2 = o2b < 4u ? dBv[o2b] : 0.0;
-                const bool sym = p1 != p2;
-                P[idx * R + t] = a1 * b2 + (sym ? a2 * b1 : 0.0);
-                Pa[idx * R + t] = da1 * b2 + (sym ? da2 * b1 : 0.0);
-                if (centre)
-                    Pb[idx * R + t] = a1 * db2 + (sym ? a2 * db1 : 0.0);
-            }
-        }
-        for (int q = 0; q < nb3; ++q) {
-            const unsigned o = (unsigned)(q - fs);
-            C[q * R + t] = o < 4u ? Cw[o] : 0.0;
-            dC[q * R + t] = o < 4u ? dCw[o] : 0.0;
-        }
-    };
-    // every lane adds a batch of triplet records to its own columns
-    auto consume3 = [&](int nrec) {
-        for (int t = 0; t < nrec; ++t) {
-            const int z = RZ[t];
-            if (z < 0)
-                continue;
-            const bool centre = RC[t] != 0;
-            const double v1[3] = {V[t], V[R + t], V[2 * R + t]};
-            const double v2[3] = {V[3 * R + t], V[4 * R + t], V[5 * R + t]};
-            for (int mm = 0; mm < kFitColsPerLane; ++mm) {
-                const FitCol &c = col[mm];
-                if (c.kind != 3 || c.a != z)
-                    continue;
-                const double u = P[c.p * R + t], ua = Pa[c.p * R + t];
-                const double cs = C[c.s * R + t];
-                const double X = ua * cs;
-                double Y;
-                if (centre) {
-                    Y = Pb[c.p * R + t] * cs;
-                    e[mm] += u * cs;
-                } else {
-                    Y = u * dC[c.s * R + t];
-                }
-                for (int k = 0; k < 3; ++k)
-                    f[mm][k] += X * v1[k] + Y * v2[k];
-            }
-        }
-    };
-
-    if (three && m > 0) {
-        // 2. triplets centred on i: unordered leg pairs (a < b)
-        const int npairs = m * (m - 1) / 2;
-        for (int base = 0; base < npairs; base += R) {
-            const int t = base + lane;
-            if (lane < R) {
-                RZ[lane] = -1;
-                if (t < npairs) {
-                    int a = 0, rem = t;
-                    while (rem >= m - 1 - a) {
-                        rem -= m - 1 - a;
-                        ++a;
-                    }
-                    const int b = a + 1 + rem;
-                    const FitLeg &Ga = leg[a], &Gb = leg[b];
-                    double dd[3];
-                    for (int k = 0; k < 3; ++k)
-                        dd[k] = Gb.d[k] - Ga.d[k];
-                    const double rjk = sqrt(dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2]);
-                    int fs;
-                    double Cw[4], dCw[4];
-                    fit_bspline(rjk, sh.nk3, sh.ih3c, fs, Cw, dCw);
-                    put(lane, Ga.f, Ga.B, Ga.dB, Gb.f, Gb.B, Gb.dB, fs, Cw, dCw, true);
+        if constexpr (three) {
+            const int at = m + __popcll(m3 & ((1ull << lane) - 1ull));
+            if (in3) {
+                if (at < kFitLegs) {
+                    FitLeg &G = leg[at];
+                    G.j = j;
+                    G.z = sp_clamp(species[j], sh.ns);
+                    const double ir = 1.0 / r;
                     for (int k = 0; k < 3; ++k) {
-                        V[k * R + lane] = Ga.d[k] * Ga.ir;
-                        V[(3 + k) * R + lane] = Gb.d[k] * Gb.ir;
+                        G.d[k] = d[k];
+                        G.u[k] = d[k] * ir;
                     }
-                    RZ[lane] = zi;
-                    RC[lane] = 1;
+                    int f;
+                    double B[4], dB[4];
+                    fit_bspline(r, NF3 + 1, sh.ih3, f, B, dB);
+#pragma unroll
+                    for (int k = 0; k < 5; ++k) {
+                        G.B[k] = 0.0;
+                        G.dB[k] = 0.0;
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (f + k < NF3) {
+                            G.B[f + k] = B[k];
+                            G.dB[f + k] = dB[k];
+                        }
+                } else {
+                    atomicOr(&hdr[H_STATUS], MLMIX_STATUS_TRIPLET_OVERFLOW);
                 }
             }
-            __syncthreads();
-            consume3(npairs - base < R ? npairs - base : R);
-            __syncthreads();
+            m = min(m + __popcll(m3), kFitLegs);
+        }
+        fit_wave_sync();
+        const int row = lane & 3;
+        for (int k0 = 0; k0 < nv4; k0 += 16) {
+            // four steps, their operands read first (masked steps add zeros)
+            const double *q[4];
+            int zr[4];
+            double av[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int s = min(k0 + 4 * v, nv4 - 4) + kg;
+                q[v] = rec + s * rs2;
+                zr[v] = k0 + 4 * v < nv4 ? rz[s] : -1;
+                av[v] = row < 3 ? q[v][2 * nf2 + row] : 0.0;
+            }
+            const double ae = row == 3 ? 0.5 : 0.0;
+#pragma unroll
+            for (int t = 0; t < T2; ++t)
+                if (t < nt2) {
+                    double bd[4], bv[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        bd[v] = q[v][nf2 + col2[t]];
+                        bv[v] = q[v][col2[t]];
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const bool on = zr[v] == need[t];
+                        acc2[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[v], on ? bd[v] : 0.0, acc2[t], 0, 0, 0);
+                        acc2[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(ae, on ? bv[v] : 0.0, acc2[t], 0, 0, 0);
+                    }
+                }
+        }
+        fit_wave_sync();
+    }
+    // lane holds [row kg (component, or energy)][column 16 t + l16]
+#pragma unroll
+    for (int t = 0; t < T2; ++t) {
+        const int c = 16 * t + l16;
+        if (c < sh.n2cols) {
+            if (kg < 3)
+                rows[(size_t)(1 + (size_t)kg * n + i) * ld + c] = acc2[t];
+            else
+                erow[(size_t)c * n + i] = acc2[t];
+        }
+    }
+
+    if constexpr (three) {
+        const int l4 = lane & 3, blk = (lane >> 2) & 3;
+        // rows of the leg-pair products: (p1, p2) = row l16, inner index p =
+        // kg; gi selects the leg function that meets T[p] there (4: none)
+        int gi = 4;
+        {
+            int idx = 0;
+#pragma unroll
+            for (int p1 = 0; p1 < NF3; ++p1)
+#pragma unroll
+                for (int p2 = p1; p2 < NF3; ++p2, ++idx)
+                    if (idx == l16)
+                        gi = kg == p2 ? p1 : (kg == p1 ? p2 : 4);
+        }
+        // columns c = (species, third side): 4 g + l4 of the results, and 4 blk
+        // + l4 where the blocks are the column groups
+        int cz[CG], cs[CG];
+#pragma unroll
+        for (int g = 0; g < CG; ++g) {
+            const int c = 4 * g + l4;
+            cz[g] = c < sh.ns * NB3 ? c / NB3 : -2;
+            cs[g] = c % NB3;
+        }
+        const int cb = 4 * blk + l4;
+        const bool onb = cb < sh.ns * NB3 && cb / NB3 == zi;
+        const int csb = cb % NB3;
+        double accF[3][CG], accE[CG];
+#pragma unroll
+        for (int g = 0; g < CG; ++g) {
+            accE[g] = 0.0;
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                accF[q][g] = 0.0;
         }
 
-        // 3. triplets centred on a 3-body neighbour j with i as one leg: the
-        // other leg k runs over j's own 3-body list (k != i)
-        if (lane == 0) {
-            int acc = 0;
-            for (int a = 0; a < m; ++a) {
-                legpre[a] = acc;
-                acc += l3cnt[leg[a].j];
+        // ---- 2. triplets centred on i: for each leg a the other legs b (a
+        // multiple of four slots per a; unused ones hold zeros)
+        const int mp = (m + 3) & ~3;
+        {
+            double tc = 0.0;
+            int a = 0, end = mp;
+            auto flush = [&]() {
+                const FitLeg &G = leg[a];
+                const double ga = 0.5 * G.B[gi], gd = G.dB[gi];  // T counts a pair twice
+                double t[CG];
+                t[0] = fit_from_block<0>(tc);
+                if constexpr (CG > 1)
+                    t[1] = fit_from_block<1>(tc);
+                if constexpr (CG > 2)
+                    t[2] = fit_from_block<2>(tc);
+#pragma unroll
+                for (int g = 0; g < CG; ++g) {
+                    accE[g] = __builtin_amdgcn_mfma_f64_4x4x4f64(ga, t[g], accE[g], 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        accF[q][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(gd * G.u[q], t[g], accF[q][g], 0, 0, 0);
+                }
+                tc = 0.0;
+                ++a;
+                end += mp;
+            };
+            const int total = m * mp;
+            for (int base = 0; base < total; base += kFitRec) {
+                const int nr = min(kFitRec, total - base);
+                if (lane < nr) {
+                    const int ra = (base + lane) / mp, rb = base + lane - ra * mp;
+                    double *q = rec + lane * FD::RC;
+#pragma unroll
+                    for (int k = 0; k < NB3; ++k)
+                        q[k] = 0.0;
+                    if (rb < m && rb != ra) {
+                        double dd[3];
+                        for (int k = 0; k < 3; ++k)
+                            dd[k] = leg[rb].d[k] - leg[ra].d[k];
+                        const double r = sqrt(dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2]);
+                        int f;
+                        double N[4], dN[4];
+                        fit_bspline(r, NF3 + 1, sh.ih3c, f, N, dN);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            q[f + k] = N[k];
+                    }
+                }
+                fit_wave_sync();
+                // up to four steps of one leg at a time, their operands read
+                // before the first (masked steps add zeros)
+                for (int k0 = 0; k0 < nr;) {
+                    if (base + k0 == end)
+                        flush();
+                    const int ns4 = min(min(16, nr - k0), end - base - k0);
+                    double av[4], bv[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int s = min(k0 + 4 * v, nr - 4) + kg;
+                        av[v] = leg[min(base + s - (end - mp), m - 1)].B[l4];
+                        bv[v] = rec[s * FD::RC + csb];
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        tc = __builtin_amdgcn_mfma_f64_4x4x4f64(av[v], onb && 4 * v < ns4 ? bv[v] : 0.0, tc, 0, 0, 0);
+                    k0 += ns4;
+                }
+                fit_wave_sync();
             }
-            legpre[m] = acc;
+            if (m > 0)
+                flush();
         }
-        __syncthreads();
-        const int total = legpre[m];
-        for (int base = 0; base < total; base += R) {
-            const int t = base + lane;
-            if (lane < R) {
-                RZ[lane] = -1;
-                if (t < total) {
-                    int a = 0;
-                    while (legpre[a + 1] <= t)
-                        ++a;
-                    const FitLeg &Ga = leg[a];
-                    const int j = Ga.j;
-                    const int k = l3[(size_t)j * kMaxTriplet + (t - legpre[a])];
+
+        // ---- 3. triplets centred on a 3-body neighbour j with i as one leg:
+        // the other leg k runs over j's own 3-body list (k != i), again a
+        // multiple of four slots per j
+        const int own = lane < m ? l3cnt[leg[lane].j] : 0, pad = (own + 3) & ~3;
+        int pre = pad;
+        for (int o = 1; o < kFitLegs; o <<= 1) {
+            const int v = __shfl_up(pre, o);
+            pre += lane >= o ? v : 0;
+        }
+        if (lane < m) {
+            legpre[lane] = pre - pad;
+            rz[lane] = own;
+        }
+        const int total = __shfl(pre, kFitLegs - 1);
+        if (lane == 0)
+            legpre[m] = total;
+        fit_wave_sync();
+        {
+            double t[CG];
+#pragma unroll
+            for (int g = 0; g < CG; ++g)
+                t[g] = 0.0;
+            int a = 0, end = m > 0 ? legpre[1] : 0;
+            int fb[CG];  // this lane's right operand: C (block 0) or its derivative
+#pragma unroll
+            for (int g = 0; g < CG; ++g)
+                fb[g] = (blk == 0 ? FD::C : FD::E) + cs[g];
+            auto flush = [&]() {
+                const FitLeg &G = leg[a];
+                const double ga = G.B[gi], gd = G.dB[gi];
+#pragma unroll
+                for (int g = 0; g < CG; ++g) {
+                    const double t0 = fit_from_block<0>(t[g]);
+                    const double tq[3] = {fit_from_block<1>(t[g]), fit_from_block<2>(t[g]),
+                                          fit_from_block<3>(t[g])};
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        accF[q][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(gd * G.u[q], t0, accF[q][g], 0, 0, 0);
+                        accF[q][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(ga, tq[q], accF[q][g], 0, 0, 0);
+                    }
+                    t[g] = 0.0;
+                }
+                ++a;
+                end = legpre[min(a + 1, m)];
+            };
+            // the partner of a slot and both positions are read a batch ahead
+            int ra = 0, k = -1;
+            double xj[3], xk[3];
+            auto fetch = [&](int tt) {
+                ra = 0;  // the last leg whose slots start at or before tt
+                k = -1;
+                if (tt >= total)
+                    return;
+                for (int w = kFitLegs / 2; w > 0; w >>= 1)
+                    if (ra + w < m && legpre[ra + w] <= tt)
+                        ra += w;
+                const int j = leg[ra].j, idx = tt - legpre[ra];
+                if (idx < rz[ra])
+                    k = l3[(size_t)j * kMaxTriplet + idx];
+                const int kc = k >= 0 && k < n ? k : j;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    xj[c] = pos[c * n + j];
+                    xk[c] = pos[c * n + kc];
+                }
+            };
+            fetch(lane);
+            for (int base = 0; base < total; base += kFitRec) {
+                const int nr = min(kFitRec, total - base);
+                if (lane < nr) {
+                    const FitLeg &Ga = leg[ra];
+                    double *q = rec + lane * RS;
+#pragma unroll
+                    for (int c = 0; c < RS; ++c)
+                        q[c] = 0.0;
                     if (k >= 0 && k < n && k != i) {
                         double djk[3];
-                        const double r2jk = fit_disp(pos, n, j, k, box, djk);
+                        const double r2jk = fit_fold(xj, xk, box, djk);
                         if (r2jk < rc3sq) {
-                            const double rjk = sqrt(r2jk);
                             double d3[3];
-                            for (int q = 0; q < 3; ++q)
-                                d3[q] = Ga.d[q] + djk[q];
+                            for (int c = 0; c < 3; ++c)
+                                d3[c] = Ga.d[c] + djk[c];
                             const double r3 = sqrt(d3[0] * d3[0] + d3[1] * d3[1] + d3[2] * d3[2]);
-                            int fb, fs;
-                            double Bw[4], dBw[4], Cw[4], dCw[4];
-                            fit_bspline(rjk, sh.nk3, sh.ih3, fb, Bw, dBw);
-                            fit_bspline(r3, sh.nk3, sh.ih3c, fs, Cw, dCw);
-                            put(lane, Ga.f, Ga.B, Ga.dB, fb, Bw, dBw, fs, Cw, dCw, false);
-                            for (int q = 0; q < 3; ++q) {
-                                V[q * R + lane] = Ga.d[q] * Ga.ir;
-                                V[(3 + q) * R + lane] = d3[q] / r3;
+                            int f;
+                            double N[4], dN[4];
+                            fit_bspline(r3, NF3 + 1, sh.ih3c, f, N, dN);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                q[FD::C + f + c] = N[c];
+                                q[FD::E + f + c] = dN[c];
                             }
-                            RZ[lane] = Ga.z;
-                            RC[lane] = 0;
+                            fit_bspline(sqrt(r2jk), NF3 + 1, sh.ih3, f, N, dN);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                if (f + c < NF3)
+                                    q[FD::B + f + c] = N[c];
+                            const double ir3 = 1.0 / r3;
+                            q[FD::W] = 1.0;
+#pragma unroll
+                            for (int c = 0; c < 3; ++c)
+                                q[FD::W + 1 + c] = d3[c] * ir3;
                         }
                     }
                 }
+                fetch(base + kFitRec + lane);
+                fit_wave_sync();
+                for (int k0 = 0; k0 < nr;) {
+                    while (base + k0 >= end)
+                        flush();
+                    const int ns4 = min(min(16, nr - k0), end - base - k0);
+                    const int zj = leg[a].z;
+                    double av[4], bv[4][CG];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const double *q = rec + (min(k0 + 4 * v, nr - 4) + kg) * RS;
+                        av[v] = q[FD::B + l4] * q[FD::W + blk];
+#pragma unroll
+                        for (int g = 0; g < CG; ++g)
+                            bv[v][g] = q[fb[g]];
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+#pragma unroll
+                        for (int g = 0; g < CG; ++g)
+                            t[g] = __builtin_amdgcn_mfma_f64_4x4x4f64(
+                                av[v], cz[g] == zj && 4 * v < ns4 ? bv[v][g] : 0.0, t[g], 0, 0, 0);
+                    k0 += ns4;
+                }
+                fit_wave_sync();
             }
-            __syncthreads();
-            consume3(total - base < R ? total - base : R);
-            __syncthreads();
+            if (a < m)
+                flush();
         }
-    }
-
-    for (int mm = 0; mm < kFitColsPerLane; ++mm) {
-        const int k = lane + kFitWave * mm;
-        if (k >= sh.nd)
-            break;
-        erow[(size_t)k * n + i] = e[mm];
-        for (int q = 0; q < 3; ++q)
-            rows[(size_t)(1 + (size_t)q * n + i) * ld + k] = f[mm][q];
+        // lane holds [row 4 blk + kg = leg pair][column 4 g + l4]
+        const int pq = 4 * blk + kg;
+#pragma unroll
+        for (int g = 0; g < CG; ++g) {
+            if (cz[g] < 0 || pq >= NPQ)
+                continue;
+            const int c = sh.n2cols + (cz[g] * NPQ + pq) * NB3 + cs[g];
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                rows[(size_t)(1 + (size_t)q * n + i) * ld + c] = accF[q][g];
+            erow[(size_t)c * n + i] = accE[g];
+        }
     }
 }
 
@@ -606,7 +760,24 @@ void launch_fit_design(hipStream_t s, const Ctx &c, const FitCfgHost *cfg, int n
         Bt.atom0[Bt.ncfg] = atoms;
         if (sh.nk3 > 1)
             k_fit_list3<<<atoms, kFitWave, 0, s>>>(Bt, sh.rc3 * sh.rc3);
-        k_fit_design<<<atoms, kFitWave, fit_design_lds(sh.nk2, sh.nk3), s>>>(Bt, sh);
+        auto go = [&](auto nf, auto cg) {
+            using FD = FitDims<decltype(nf)::value, decltype(cg)::value>;
+            const size_t rs2 = fit_pair_stride(sh.nk2 - 1) * sizeof(double);
+            // pair records per batch: 64 unless many knots make them long
+            const int rb2 = rs2 * 64 <= 32 * 1024 ? 64 : (rs2 * 32 <= 32 * 1024 ? 32 : 16);
+            size_t lds = rs2 * rb2;
+            if (sh.nk3 > 1)
+                lds = std::max(lds, (size_t)kFitRec * FD::RS * sizeof(double));
+            k_fit_design<decltype(nf)::value, decltype(cg)::value><<<atoms, kFitWave, lds, s>>>(Bt, sh, rb2);
+        };
+        if (sh.nk3 <= 1)
+            go(std::integral_constant<int, 0>(), std::integral_constant<int, 1>());
+        else if (sh.nk3 == 5)
+            go(std::integral_constant<int, 4>(), std::integral_constant<int, 2>());
+        else if (sh.ns == 1)
+            go(std::integral_constant<int, 3>(), std::integral_constant<int, 2>());
+        else
+            go(std::integral_constant<int, 3>(), std::integral_constant<int, 3>());
         k_fit_erow_sum<<<dim3(nd, Bt.ncfg), 256, 0, s>>>(Bt);
     }
 }
@@ -786,14 +957,6 @@ __device__ __forceinline__ double fit_wave_sum(double v)
     for (int o = 32; o > 0; o >>= 1)
         v += __shfl_xor(v, o);
     return v;
-}
-
-// Orders one wavefront's LDS writes before its later LDS reads.
-__device__ __forceinline__ void fit_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Block sum over 256 threads in a fixed order.
