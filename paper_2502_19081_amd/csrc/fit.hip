@@ -952,6 +952,32 @@ struct FitSearchArgs {
     double *c, *info;
 };
 
+typedef double fit_d4 __attribute__((ext_vector_type(4)));
+
+// v of lane l (the same l on every lane)
+__device__ __forceinline__ double fit_readlane(double v, int l)
+{
+    union {
+        double d;
+        int w[2];
+    } x{v};
+    x.w[0] = __builtin_amdgcn_readlane(x.w[0], l);
+    x.w[1] = __builtin_amdgcn_readlane(x.w[1], l);
+    return x.d;
+}
+
+// 1/sqrt(t) for t > 0: the hardware estimate and two Newton steps
+__device__ __forceinline__ double fit_rsqrt(double t)
+{
+    double y = __builtin_amdgcn_rsq(t);
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const double e = fma(-t * y, y, 1.0);
+        y = fma(y * e, fma(e, 0.375, 0.5), y);
+    }
+    return y;
+}
+
 __device__ __forceinline__ double fit_wave_sum(double v)
 {
     for (int o = 32; o > 0; o >>= 1)
@@ -959,128 +985,208 @@ __device__ __forceinline__ double fit_wave_sum(double v)
     return v;
 }
 
-// Block sum over 256 threads in a fixed order.
-__device__ double fit_block_sum(double v, double *red)
-{
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    const double s = red[0];
-    __syncthreads();
-    return s;
-}
-
 __global__ void __launch_bounds__(256) k_fit_search(FitSearchArgs a)
 {
     // packed lower triangle of M plus the right-hand side as an extra row nd
     // (factorising that row performs the forward substitution)
     constexpr int kPacked = (kFitMaxParams + 1) * (kFitMaxParams + 2) / 2;
-    __shared__ double Lp[kPacked];
+    // (sixteen entries past its end are read and not used, the last written
+    // by lanes with nothing to store: the masked accesses need no branch)
+    constexpr int kDump = kPacked + 16;
+    __shared__ double Lp[kDump + 1];
     __shared__ double cur[kFitMaxParams], keep[kFitMaxParams], rdg[kFitMaxParams];
-    __shared__ double red[256];
+    __shared__ double red[4];
     __shared__ int fail;
     const int nd = a.nd, tid = threadIdx.x;
     auto P = [](int r, int c2) { return r * (r + 1) / 2 + c2; };  // r >= c2
-
-
+    const int wv = tid >> 6, ln = tid & 63, kg = ln >> 4, l16 = ln & 15;
+    // this thread's entries of the packed triangle: offset in the square
+    // matrices, bit 16 on the diagonal
+    constexpr int kOwn = (kFitMaxParams * (kFitMaxParams + 1) / 2 + 255) / 256;
+    int own[kOwn];
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+        const int e = min(tid + 256 * u, nd * (nd + 1) / 2 - 1);
+        int r = (int)((sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
+        while (r * (r + 1) / 2 > e)
+            --r;
+        while ((r + 1) * (r + 2) / 2 <= e)
+            ++r;
+        const int c2 = e - r * (r + 1) / 2;
+        own[u] = (r * nd + c2) | (r == c2 ? 1 << 16 : 0);
+    }
     // one solve at lam: cur = c(lam); returns the hard residual (or -1 when
     // the factorisation meets a non-positive pivot)
     auto solve = [&](double lam) -> double {
-        for (int e = tid; e < nd * (nd + 1) / 2; e += 256) {
-            int r = (int)((sqrt(8.0 * (double)e + 1.0) - 1.0) * 0.5);
-            while (r * (r + 1) / 2 > e)
-                --r;
-            while ((r + 1) * (r + 2) / 2 <= e)
-                ++r;
-            const int c2 = e - r * (r + 1) / 2;
-            double v = a.GS[(size_t)r * nd + c2] + lam * a.GH[(size_t)r * nd + c2];
-            if (r == c2)
-                v += a.ridge;
-            Lp[e] = v;
+        double gs[kOwn], gh[kOwn];
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u) {  // every load in flight before the first use
+            const int e = own[u] & 0xffff;
+            gs[u] = a.GS[e];
+            gh[u] = a.GH[e];
         }
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u)
+            if (tid + 256 * u < nd * (nd + 1) / 2)
+                Lp[tid + 256 * u] = gs[u] + lam * gh[u] + (own[u] >> 16 ? a.ridge : 0.0);
         if (tid < nd)
             Lp[P(nd, tid)] = a.bS[tid] + lam * a.bH[tid];
         if (tid == 0)
             fail = 0;
         __syncthreads();
-        // left-looking Cholesky, column by column. The unnormalised column
-        // is written first; every thread then scales its own entry by
-        // 1/sqrt(t_jj) (kept in rdg), so a column needs two barriers. The
-        // diagonal of Lp keeps t_jj; the substitutions use rdg.
-        for (int j = 0; j < nd; ++j) {
-            const int i = j + tid;  // rows j .. nd (nd = right-hand side); nd < 256
-            double t = 0.0;
-            if (i <= nd) {
-                // four partial sums so that the LDS loads of later terms are
-                // in flight while earlier ones accumulate
-                const double *li = Lp + P(i, 0), *lj = Lp + P(j, 0);
-                double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0;
-                int k = 0;
-                for (; k + 4 <= j; k += 4) {
-                    t0 += li[k] * lj[k];
-                    t1 += li[k + 1] * lj[k + 1];
-                    t2 += li[k + 2] * lj[k + 2];
-                    t3 += li[k + 3] * lj[k + 3];
+        // Cholesky in panels of 16 columns, row nd (the right-hand side) carried
+        // along. Within a panel every lane holds one row's 16 entries: lanes
+        // 0 .. 15 of each wavefront the diagonal block (all four the same),
+        // the others 48 rows below it, so that a column needs no barrier: its
+        // pivot and multipliers are read from the block's lanes. The trailing
+        // matrix then takes 16x16x4 FP64 matrix steps. (One column at a time
+        // with two barriers each: 115 us per solve at 81 parameters; panels:
+        // 33 us.)
+        for (int k0 = 0; k0 < nd; k0 += 16) {
+            const int nbk = min(16, nd - k0);
+            const int row = ln < 16 ? k0 + ln : k0 + ln + 48 * wv;
+            const bool live = row <= nd;
+            double *Lr = Lp + P(min(row, nd), 0) + k0;
+            double x[16];
+#pragma unroll
+            for (int c = 0; c < 16; ++c)
+                x[c] = Lr[c];
+#pragma unroll
+            for (int c = 0; c < 16; ++c)
+                x[c] = live && c < nbk && k0 + c <= row ? x[c] : 0.0;
+            double rj = 1.0;  // lane j: 1/L_jj of column k0 + j
+            bool bad = false;
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                if (j < nbk) {  // uniform
+                    const double tj = fit_readlane(x[j], j);
+                    const double r = tj > 0.0 ? fit_rsqrt(tj) : 1.0;
+                    const double l = x[j] * r;
+                    x[j] = l;
+#pragma unroll
+                    for (int c = j + 1; c < 16; ++c)
+                        x[c] -= l * fit_readlane(l, c);
+                    rj = ln == j ? r : rj;
+                    bad = bad || !(tj > 0.0);
                 }
-                for (; k < j; ++k)
-                    t0 += li[k] * lj[k];
-                t = Lp[P(i, j)] - ((t0 + t1) + (t2 + t3));
-                Lp[P(i, j)] = t;
-            }
+            if (tid < nbk)
+                rdg[k0 + tid] = rj;
+            if (tid == 0 && bad)
+                fail = 1;
+            __syncthreads();  // every wavefront has read its rows
+            const bool keeps = live && (ln >= 16 || wv == 0);
+#pragma unroll
+            for (int c = 0; c < 16; ++c)
+                *(keeps && c < nbk && k0 + c < row ? Lr + c : Lp + kDump) = x[c];
             __syncthreads();
-            const double tj = Lp[P(j, j)];
-            const double r = tj > 0.0 ? 1.0 / sqrt(tj) : 1.0;
-            if (i > j && i <= nd)
-                Lp[P(i, j)] = t * r;
-            if (tid == 0) {
-                if (!(tj > 0.0))
-                    fail = 1;
-                rdg[j] = r;
+            const int t0 = k0 + 16, nt = t0 <= nd ? (nd - t0) / 16 + 1 : 0;
+            for (int t = wv, ti = 0, tj = wv; t < nt * (nt + 1) / 2; t += 4, tj += 4) {
+                while (tj > ti) {  // tile (ti, tj), tj <= ti, row by row
+                    tj -= ti + 1;
+                    ++ti;
+                }
+                const int i0 = t0 + 16 * ti, j0 = t0 + 16 * tj;
+                const int ia = i0 + l16, jb = j0 + l16;
+                const double *La = Lp + P(min(ia, nd), 0) + k0 + kg;
+                const double *Lb = Lp + P(min(jb, nd), 0) + k0 + kg;
+                double av[4], bv[4], cv[4];
+                double *Lc[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + 4 * u + kg;
+                    Lc[u] = i <= nd && jb < nd && jb <= i ? Lp + P(i, jb) : Lp + kDump;
+                    av[u] = La[4 * u];
+                    bv[u] = Lb[4 * u];
+                    cv[u] = *Lc[u];
+                }
+                fit_d4 acc = {cv[0], cv[1], cv[2], cv[3]};
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[u], bv[u], acc, 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    *Lc[u] = acc[u];
             }
             __syncthreads();
         }
         // row nd now holds x with L x = b; L^T c = x by wavefront 0, column
-        // by column (c_j = x_j / L_jj, then x_k -= L_jk c_j for k < j)
-        if (tid < 64) {
-            for (int k = tid; k < nd; k += 64)
-                cur[k] = Lp[P(nd, k)];
-            fit_wave_sync();
-            for (int j = nd - 1; j >= 0; --j) {
-                if (tid == 0)
-                    cur[j] = cur[j] * rdg[j];
-                fit_wave_sync();
-                const double cj = cur[j];
-                for (int k = tid; k < j; k += 64)
-                    cur[k] -= Lp[P(j, k)] * cj;
-                fit_wave_sync();
-            }
-        }
-        __syncthreads();
-        // hard residual: each wavefront takes four rows at a time, lanes
-        // over the parameters
-        double part = 0.0;
-        const int wv = tid >> 6, ln = tid & 63;
-        for (int h0 = 4 * wv; h0 < a.nh; h0 += 16) {
-            double r[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int k = ln; k < nd; k += 64) {
-                const double ck = cur[k];
-                for (int q = 0; q < 4; ++q)
-                    if (h0 + q < a.nh)
-                        r[q] += a.AH[(size_t)(h0 + q) * a.ldh + k] * ck;
-            }
-            for (int q = 0; q < 4; ++q) {
-                const double rq = fit_wave_sum(r[q]);
-                if (ln == 0 && h0 + q < a.nh) {
-                    const double d = rq - a.yH[h0 + q];
-                    part += (a.wH ? a.wH[h0 + q] : 1.0) * d * d;
+        // by column (c_j = x_j / L_jj, then x_k -= L_jk c_j for k < j): x and
+        // 1/L_jj in registers, four rows of L read ahead of their columns
+        if (wv == 0) {
+            const int lo = min(ln, nd - 1), hi = min(ln + 64, nd - 1);
+            double x0 = Lp[P(nd, lo)], x1 = Lp[P(nd, hi)];
+            const double d0 = rdg[lo], d1 = rdg[hi];
+            double c0 = 0.0, c1 = 0.0;
+            for (int j0 = nd - 1; j0 >= 64; j0 -= 4) {  // columns 64 and up
+                double l0[4], l1[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double *Lj = Lp + P(max(j0 - u, 64), 0);
+                    l0[u] = Lj[ln];
+                    l1[u] = Lj[min(ln + 64, max(j0 - u, 64))];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int j = j0 - u, jl = max(j - 64, 0);
+                    const double v = fit_readlane(x1, jl) * fit_readlane(d1, jl);
+                    const double cj = j >= 64 ? v : 0.0;
+                    c1 = ln + 64 == j ? cj : c1;
+                    x0 -= l0[u] * cj;
+                    x1 -= ln + 64 < j ? l1[u] * cj : 0.0;
                 }
             }
+            for (int j0 = min(nd, 64) - 1; j0 >= 0; j0 -= 4) {
+                double l0[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    l0[u] = Lp[P(max(j0 - u, 0), min(ln, max(j0 - u, 0)))];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int j = j0 - u, jl = max(j, 0);
+                    const double v = fit_readlane(x0, jl) * fit_readlane(d0, jl);
+                    const double cj = j >= 0 ? v : 0.0;
+                    c0 = ln == j ? cj : c0;
+                    x0 -= ln < j ? l0[u] * cj : 0.0;
+                }
+            }
+            if (ln < nd)
+                cur[ln] = c0;
+            if (ln + 64 < nd)
+                cur[ln + 64] = c1;
         }
-        const double res = fit_block_sum(part, red);
+        __syncthreads();
+        // hard residual: A_H c for 16 rows per wavefront and pass as 4x4x4 FP64
+        // matrix steps (every column of the right operand is c), a pass's loads
+        // eight steps ahead
+        double part = 0.0;
+        for (int h0 = 16 * wv; h0 < a.nh; h0 += 64) {
+            const double *src = a.AH + (size_t)min(h0 + l16, a.nh - 1) * a.ldh;
+            double r = 0.0;
+            for (int k0 = 0; k0 < nd; k0 += 32) {
+                double av[8], cv[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int k = k0 + 4 * u + kg;
+                    av[u] = src[min(k, nd - 1)];
+                    cv[u] = k < nd ? cur[k] : 0.0;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    r = __builtin_amdgcn_mfma_f64_4x4x4f64(av[u], cv[u], r, 0, 0, 0);
+            }
+            // lane holds row 4 (lane / 4 % 4) + kg (the same in four columns)
+            const int h = h0 + 4 * ((ln >> 2) & 3) + kg;
+            if ((ln & 3) == 0 && h < a.nh) {
+                const double d = r - a.yH[h];
+                part += (a.wH ? a.wH[h] : 1.0) * d * d;
+            }
+        }
+        const double ps = fit_wave_sum(part);
+        if (ln == 0)
+            red[wv] = ps;
+        __syncthreads();
+        const double res = (red[0] + red[1]) + (red[2] + red[3]);
+        __syncthreads();
         return fail ? -1.0 : res;
     };
     auto save = [&]() {
@@ -1089,65 +1195,64 @@ __global__ void __launch_bounds__(256) k_fit_search(FitSearchArgs a)
         __syncthreads();
     };
 
-    int nsolve = 0, status = 0, dec = 0;
-    double lam = a.lam0;
-    double res = solve(lam);
-    ++nsolve;
-    double best_res = res, best_lam = lam, lam_lo = lam, out_lam = lam, out_res = res;
-    save();
-    if (res < 0.0) {
-        status = 3;
-    } else if (res > a.alpha) {
-        while (res > a.alpha && dec < a.max_decades && res >= 0.0) {
-            lam_lo = lam;
-            lam *= 10.0;
-            ++dec;
-            res = solve(lam);
-            ++nsolve;
-            if (res >= 0.0 && res < best_res) {
+    // the search as one loop around one solve (its code is long: a copy per
+    // call site would not fit the instruction cache): the first lambda, decades
+    // until the residual is at most alpha, then bisection
+    int nsolve = 0, status = 0, dec = 0, it = 0;
+    bool bisect = false;
+    double lam = a.lam0, lam_lo = lam, out_lam = lam, out_res = 0.0, best_res = 0.0, best_lam = lam;
+    double lo = lam, hi = lam, r_hi = 0.0;
+    for (;;) {
+        const double res = solve(lam);
+        ++nsolve;
+        if (!bisect) {
+            if (nsolve == 1 || (res >= 0.0 && res < best_res)) {
                 best_res = res;
                 best_lam = lam;
                 save();
             }
-        }
-        if (res < 0.0) {
-            status = 3;
-            out_lam = best_lam;
-            out_res = best_res;
-        } else if (res > a.alpha) {
-            status = 1;
-            out_lam = best_lam;
-            out_res = best_res;
-        } else {
-            // bisection: lo fails, hi passes (keep holds c(hi))
-            double lo = lam_lo, hi = lam, r_hi = res;
-            save();
-            int it = 0;
-            while (!(a.alpha - r_hi < a.tol)) {
-                if (it == a.max_bisect) {
-                    status = 2;
-                    break;
-                }
-                const double mid = 0.5 * (lo + hi);
-                const double rm = solve(mid);
-                ++nsolve;
-                if (rm < 0.0) {
-                    status = 3;
-                    break;
-                }
-                if (rm <= a.alpha) {
-                    hi = mid;
-                    r_hi = rm;
-                    save();
-                } else {
-                    lo = mid;
-                }
-                ++it;
+            if (res > a.alpha && dec < a.max_decades) {
+                lam_lo = lam;
+                lam *= 10.0;
+                ++dec;
+                continue;
             }
-            out_lam = hi;
-            out_res = r_hi;
-            lam_lo = lo;
+            out_lam = best_lam;
+            out_res = best_res;
+            if (res < 0.0 || res > a.alpha) {
+                status = res < 0.0 ? 3 : 1;
+                break;
+            }
+            if (dec == 0)
+                break;
+            // lo fails, hi passes (keep holds c(hi))
+            lo = lam_lo;
+            hi = lam;
+            r_hi = res;
+            save();
+            bisect = true;
+        } else {
+            if (res < 0.0) {
+                status = 3;
+            } else if (res <= a.alpha) {
+                hi = lam;
+                r_hi = res;
+                save();
+            } else {
+                lo = lam;
+            }
+            ++it;
         }
+        out_lam = hi;
+        out_res = r_hi;
+        lam_lo = lo;
+        if (status == 3 || a.alpha - r_hi < a.tol)
+            break;
+        if (it == a.max_bisect) {
+            status = 2;
+            break;
+        }
+        lam = 0.5 * (lo + hi);
     }
     if (tid < nd)
         a.c[tid] = keep[tid];

@@ -4,9 +4,11 @@ than one column tile); parameter and hard-row counts on both sides of the
 search's panels, wavefronts and row tiles.
 
 Tolerances: design rows sum at most a few hundred products of numbers of order
-one, so 1e-12 of the largest entry as in the other design tests; the search
-solves systems of condition number below 1e3, whose solutions lose at most
-n_params x condition x 1.1e-16 < 2e-11: 1e-10 of the largest coefficient.
+one, so 1e-12 of the largest entry as in the other design tests; the search's
+solutions may lose n_params x condition x 1.1e-16 of the largest coefficient
+each way. With more hard rows than parameters alpha may be out of reach: both
+then return the solution of the smallest residual seen, which is flat in lambda,
+so the residuals are compared and not lambda.
 """
 import numpy as np
 import pytest
@@ -53,5 +55,10 @@ def test_search_sizes(nd, nh):
     t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
     u, got = fit.constrained(t(G), t(b), t(AH), t(yH), alpha, lam0=1e-3, ridge=1e-3, wH=t(wH))
     assert got["status"] == info["status"] and got["n_solves"] == info["n_solves"]
+    cond = np.linalg.cond(G + info["lam"] * (AH.T @ (wH[:, None] * AH)) + 1e-3 * np.eye(nd))
+    tol = max(2 * nd * cond * 1.1e-16, 1e-13)
+    if info["status"] == 1:
+        assert abs(got["residual"] - info["residual"]) <= tol * info["residual"]
+        return
     assert abs(got["lam"] - info["lam"]) <= 1e-12 * info["lam"]
-    assert np.abs(u.cpu().numpy() - c).max() <= 1e-10 * np.abs(c).max()
+    assert np.abs(u.cpu().numpy() - c).max() <= tol * np.abs(c).max()
