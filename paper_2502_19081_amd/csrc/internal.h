@@ -36,6 +36,7 @@ enum HeaderWord {
     H_FWD = 6,        // a forward pass with dE/dA exists
     H_MOVED = 7,      // an atom moved more than half the skin since the last build
     H_NBUILD = 8,     // neighbour-list builds since the workspace was initialised
+    H_O3PURE = 9,     // S atoms of the wide contraction's first class (k_o3_order)
     H_COUNT = 64
 };
 
