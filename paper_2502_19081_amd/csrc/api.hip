@@ -1703,7 +1703,7 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
                          c.d.skin, ra, disp_checked);
     }
     // fork: reverse slots and the cheap potential need only the list; they are
-    // started after the neighbour rows (fork_at 0) or after the atomic basis
+    // started after the neighbour rows (fork_at 0, 2) or after the atomic basis
     // (fork_at 1, beside the matrix-core contraction)
     bool fork_recorded = false;
     auto record_fork = [&]() -> int {
@@ -1743,8 +1743,9 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
     // 1: both after the atomic basis
     // With the cheap potential masked its kernel needs the final masks: the
     // fork point then follows the region stage.
-    const bool late = c.fork_at == 1 && m != MLMIX_MODE_ALL_CHEAP && !masked;
-    if (c.fork_at == 2 && !masked) {
+    const int fork_at = c.fork_at >= 0 ? c.fork_at : (c.o3 && L.nseg == 0 ? 1 : 2);
+    const bool late = fork_at == 1 && m != MLMIX_MODE_ALL_CHEAP && !masked;
+    if (fork_at == 2 && !masked) {
         int rc = record_fork();
         if (rc)
             return rc;
@@ -1771,7 +1772,7 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
         StageTimer t(ctx, s, ST_CMP);
         launch_compact(s, ws, L, flags, n_expensive);
     }
-    if (c.fork_at == 2 || masked) {
+    if (fork_at == 2 || masked) {
         int rc = fork_side();
         if (rc)
             return rc;

@@ -215,12 +215,19 @@ struct Ctx {
     int basis_mfma = 1;    // atomic basis and pair adjoint on the matrix cores (FP32)
     int basis_chunks = -1; // basis in 64-slot passes: -1 above 65,536 atoms, 0 never, 1 always
     // second-stream fork after the rows (0), after the basis (1), or recorded
-    // after the rows and issued after the compaction (2). Measured per mixed
-    // step on 8,193 atoms with the workgroup pair adjoint and the cheap
-    // potential uncapped: 95.5 / 95.8 / 95.7 us at 2 against 101.0 / 101.5 /
-    // 101.8 us at 0 (alternating runs; the one-wave adjoint's longer chain
-    // preferred 0)
-    int fork_at = 2;
+    // after the rows and issued after the compaction (2); -1 automatic: 1 for a
+    // single system whose order-3 contraction runs on the matrix cores, else 2.
+    // The cheap potential's workgroups (one wave per atom, all at once) keep
+    // the few blocks of the compaction and the basis waiting when they start
+    // first, while the contraction's occupy the compute units for long enough
+    // to hide the cheap potential behind them. Per call of 20 steps, 2 against
+    // 1: 1,930 / 1,830 us at 8,191 atoms and 1,668 / 1,555 at 1,457 (one
+    // defect, FP32), 2,800 / 2,560 (FP64, 8,191); per 4 steps at 249,960 atoms
+    // with 40 defects (BF16) 7,245 / 6,720, at 1,023,800 with 200 (FP32) 37.3 /
+    // 36.1 ms. Without an order-3 contraction the chain after the basis is too
+    // short: 1,680 / 1,910 us at 21,295 atoms. A batch of 16 systems: 4,930 /
+    // 5,030 us per 5 steps (its contraction is two launches of few workgroups).
+    int fork_at = -1;
     // workgroup cap of the cheap-potential kernel on the second stream
     // (grid-stride loop): -1 automatic, 0 uncapped. The best cap follows the
     // length of the expensive chain beside it. With the one-wave pair adjoint,
