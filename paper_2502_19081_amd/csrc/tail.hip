@@ -496,6 +496,11 @@ void launch_carry_lists(hipStream_t s, void *ws_new, const WsLayout &Ln, const v
 // whichever batch. out[3 k + q] = (sum e_exp, sum e_cheap, kinetic in eV) of
 // segment k (kinetic from the per-atom 0.5 m v^2 the force gather left in
 // ke, or 0 without it); counts[2 k] = (|S|, |{lambda > 0}|) from the flags.
+// Bound by the latency of its loads, few workgroups with up to 80 rounds each:
+// kSegLoads rounds are read before the first of them is added. 16 systems of
+// 2,000 to 20,000 atoms: 37.4 -> 14.5 us (five: 22 -> 10.2).
+constexpr int kSegLoads = 8;
+
 __global__ void __launch_bounds__(256) k_seg_sums(const SegGeo *__restrict__ geo,
                                                   const double *__restrict__ e_exp,
                                                   const double *__restrict__ e_cheap,
@@ -509,15 +514,29 @@ __global__ void __launch_bounds__(256) k_seg_sums(const SegGeo *__restrict__ geo
     const SegGeo G = geo[blockIdx.x];
     double a = 0.0, b = 0.0, k = 0.0;
     int cs = 0, cm = 0;
-    for (int t = threadIdx.x; t < G.n; t += blockDim.x) {
-        const int i = G.off + t;
-        a += e_exp[i];
-        b += e_cheap[i];
-        if (ke)
-            k += ke[i];
-        const uint8_t f = flags[i];
-        cs += (f & 5) ? 1 : 0;
-        cm += (f & 1) ? 1 : 0;
+    for (int t0 = threadIdx.x; t0 < G.n; t0 += kSegLoads * blockDim.x) {
+        double ea[kSegLoads], eb[kSegLoads], ek[kSegLoads];
+        uint8_t f[kSegLoads];
+#pragma unroll
+        for (int u = 0; u < kSegLoads; ++u) {
+            const int t = t0 + u * (int)blockDim.x;
+            const int i = G.off + min(t, G.n - 1);
+            ea[u] = e_exp[i];
+            eb[u] = e_cheap[i];
+            ek[u] = ke ? ke[i] : 0.0;
+            f[u] = flags[i];
+        }
+#pragma unroll
+        for (int u = 0; u < kSegLoads; ++u) {
+            if (t0 + u * (int)blockDim.x >= G.n)
+                break;
+            a += ea[u];
+            b += eb[u];
+            if (ke)
+                k += ek[u];
+            cs += (f[u] & 5) ? 1 : 0;
+            cm += (f[u] & 1) ? 1 : 0;
+        }
     }
     a = wave_sum_d(a);
     b = wave_sum_d(b);
