@@ -1664,12 +1664,14 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
     bool fork = (mode & MLMIX_SINGLE_STREAM) == 0 && m == MLMIX_MODE_MIXED;
     const bool masked = (mode & MLMIX_CHEAP_MASKED) != 0 && m == MLMIX_MODE_MIXED;
     SideStream sd;
+    bool capturing = false;
     if (fork) {
         // the workspace's second stream is created by its first forked
         // evaluation outside a graph capture; a capture before that runs on
         // the caller's stream alone
         hipStreamCaptureStatus cst = hipStreamCaptureStatusNone;
         HIP_OK(hipStreamIsCapturing(s, &cst));
+        capturing = cst != hipStreamCaptureStatusNone;
         std::lock_guard<std::mutex> g(ctx->mu);
         SideStream &e = ctx->side[ws];
         if (!e.s && cst == hipStreamCaptureStatusNone) {
@@ -1682,10 +1684,10 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
     }
     hipStream_t s2 = fork ? sd.s : s;  // stream of the reverse slots and the cheap potential
     // workgroup cap of those two kernels when they run beside the expensive
-    // chain (MLMIX_SIDE_BLOCKS; none by default: with the workgroup pair
-    // adjoint the expensive chain of an 8,193-atom step is short enough that
-    // the cheap potential needs the whole GPU beside it, 95.7 against
-    // 100.9 us per step with one workgroup per compute unit)
+    // chain (MLMIX_SIDE_BLOCKS; none by default: forked after the basis, caps of
+    // 1,280 / 2,048 / 4,096 workgroups took 1,946 / 1,898 / 1,896 us per call of 20
+    // steps on 8,191 atoms against 1,894 without, and 40.5 / 38.0 / 37.1 against
+    // 36.1 ms per call of 4 on 1,023,800)
     const int rev_blocks = c.rev_blocks;
     const int side_blocks = (!fork || m == MLMIX_MODE_ALL_CHEAP)
                                 ? 0
@@ -1743,7 +1745,7 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
     // 1: both after the atomic basis
     // With the cheap potential masked its kernel needs the final masks: the
     // fork point then follows the region stage.
-    const int fork_at = c.fork_at >= 0 ? c.fork_at : (c.o3 && L.nseg == 0 ? 1 : 2);
+    const int fork_at = c.fork_at >= 0 ? c.fork_at : (c.o3 && L.nseg == 0 && !capturing ? 1 : 2);
     const bool late = fork_at == 1 && m != MLMIX_MODE_ALL_CHEAP && !masked;
     if (fork_at == 2 && !masked) {
         int rc = record_fork();

@@ -216,7 +216,8 @@ struct Ctx {
     int basis_chunks = -1; // basis in 64-slot passes: -1 above 65,536 atoms, 0 never, 1 always
     // second-stream fork after the rows (0), after the basis (1), or recorded
     // after the rows and issued after the compaction (2); -1 automatic: 1 for a
-    // single system whose order-3 contraction runs on the matrix cores, else 2.
+    // single system whose order-3 contraction runs on the matrix cores and whose
+    // steps are not captured, else 2.
     // The cheap potential's workgroups (one wave per atom, all at once) keep
     // the few blocks of the compaction and the basis waiting when they start
     // first, while the contraction's occupy the compute units for long enough
@@ -227,16 +228,13 @@ struct Ctx {
     // 36.1 ms. Without an order-3 contraction the chain after the basis is too
     // short: 1,680 / 1,910 us at 21,295 atoms. A batch of 16 systems: 4,930 /
     // 5,030 us per 5 steps (its contraction is two launches of few workgroups).
+    // Captured, the early fork wins: 88 / 99 us per step on 8,193 atoms and 6.88 /
+    // 7.57 ms on 1,023,800, 2 against 1.
     int fork_at = -1;
     // workgroup cap of the cheap-potential kernel on the second stream
-    // (grid-stride loop): -1 automatic, 0 uncapped. The best cap follows the
-    // length of the expensive chain beside it. With the one-wave pair adjoint,
-    // per mixed step on 8,193 atoms: 160 / 129 / 111 / 123 / 120 / 120 / 126
-    // us at 128 / 192 / 256 / 384 / 512 / 1024 workgroups / uncapped; with
-    // the shorter chain of the workgroup pair adjoint (fork point 2): 95.7 /
-    // 96.1 us uncapped / 768 against 100.9 us at 256. On 1,023,800 atoms caps
-    // of 1024 and 2048 measured no better than none (11.6 / 11.2 / 11.3 ms).
-    // Automatic: uncapped.
+    // (grid-stride loop): -1 automatic, 0 uncapped. Automatic: uncapped (caps
+    // of 1,280 to 4,096 workgroups measured no better on 8,191 atoms and 3-12 %
+    // slower on 1,023,800; only 54,000 atoms gained, 2 % at 2,048).
     int side_blocks = -1;
     int rev_blocks = 1024;  // cap of the reverse-slot kernel when capped (256 / 1024 measured 153.0 / 152.4 us)
     int o3_nch2 = 0;       // row width of that kernel (channels rounded up to 4)
