@@ -1742,7 +1742,7 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
     // fork_at 0: side kernels issued right after the rows; 2: fork point
     // recorded after the rows, side kernels issued after the compaction (so
     // that a captured graph keeps the expensive chain on the first queue);
-    // 1: both after the atomic basis
+    // 1: recorded after the atomic basis, issued after the contraction
     // With the cheap potential masked its kernel needs the final masks: the
     // fork point then follows the region stage.
     const int fork_at = c.fork_at >= 0 ? c.fork_at : (c.o3 && L.nseg == 0 && !capturing ? 1 : 2);
@@ -1785,7 +1785,7 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
             launch_ace_basis(s, c, ws, L, b, pos, species);
         }
         if (late) {
-            int rc = fork_side();
+            int rc = record_fork();
             if (rc)
                 return rc;
         }
@@ -1793,6 +1793,11 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
             // the matrix-core contraction is one kernel: timed by its own events
             StageTimer t(ctx, s, ST_CONTRACT, c.o3 && c.prec != MLMIX_FP64);
             launch_ace_contract(s, c, ws, L, species, t.k0, t.k1);
+        }
+        if (late) {
+            int rc = fork_side();
+            if (rc)
+                return rc;
         }
         // the finalisation runs inside the pair adjoint where that kernel
         // can take it (the energy-only call keeps its own kernel)
