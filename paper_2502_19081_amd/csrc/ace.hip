@@ -22,6 +22,7 @@
 
 #include "internal.h"
 #include "basis.h"
+#include "rules.h"
 
 namespace mlmix {
 
@@ -598,13 +599,34 @@ __global__ void __launch_bounds__(256)
     }
 }
 
+// Stages an atom's dE/dA row ([lm][channel], nchp channels apart) into LDS as
+// [lm][species][NR], NR the radial count rounded up to a multiple of four and
+// the added functions' entries zero: every count then runs one of four compiled
+// forms with no guard per function, and the products with the zeros leave each
+// sum as it is. (Compiled for 8, 12 and 16 functions alone, with a guard per
+// function for the others, the guarded form took up to 342 registers in FP64
+// and 187 in FP32, now 227 and 118. All-expensive call, guarded / padded: FP64,
+// 2,000 atoms, 10 functions, lmax 5: 190 / 159 us; FP32, 71,874 atoms, lmax 6:
+// 4.05 / 3.58 ms at 10 functions, 2.71 / 2.34 ms at 6.)
+template <int NR, typename T>
+__device__ __forceinline__ void dpad_stage(T *dst, const T *__restrict__ src, const AceArgs<T> &a, T wgt,
+                                           int t, int nt)
+{
+    const int inv_ns = (65536 + a.ns - 1) / a.ns;  // exact quotients: rows < 512, ns <= 8
+    for (int e = t; e < a.L2 * a.ns * NR; e += nt) {
+        const int row = e / NR, q = e - row * NR;
+        const int lm = (row * inv_ns) >> 16, z = row - lm * a.ns;
+        dst[e] = q < a.nrad ? src[lm * a.nchp + z * a.nrad + q] * wgt : T(0);
+    }
+}
+
 // Pair adjoint in FP64, one wave per S atom: the row's valid pairs (partner in
 // S, inside the cutoff) are listed in LDS by ballot, then the lanes take them
 // 64 at a time; invalid slots get a zero gradient from their owner lane. Bound
 // by the serial chain of one pair (geometry, radial recurrence, harmonics with
 // 2 NR multiply-adds each) at the few waves an FP64 system has: lmax and the
-// usual radial counts are compiled in (NR = 0: a runtime count), so that the
-// chain holds no loop control and the dE/dA reads pair up.
+// padded radial count NR are compiled in (dpad), so that the chain holds no
+// loop control and the dE/dA reads pair up.
 // 2,000 atoms in S, lmax 4, 12 radial functions: 37 -> 14 us.
 template <int LM, int NR, bool SEG>
 __global__ void __launch_bounds__(256)
@@ -622,14 +644,14 @@ __global__ void __launch_bounds__(256)
     if (s >= nS)
         return;  // no block barrier in this kernel
     extern __shared__ __align__(16) char smem_raw[];
-    // per wave: the dE/dA row (KAt is a multiple of four), then the pair list
-    double *dAs = reinterpret_cast<double *>(smem_raw) + (size_t)w * (a.KAt + ((cap + 3) & ~3) / 2);
-    int *pl = reinterpret_cast<int *>(dAs + a.KAt);
+    // per wave: the padded dE/dA row, then the pair list
+    const int row_len = a.L2 * a.ns * NR;
+    double *dAs = reinterpret_cast<double *>(smem_raw) + (size_t)w * (row_len + ((cap + 3) & ~3) / 2);
+    int *pl = reinterpret_cast<int *>(dAs + row_len);
     const int i = S_idx[s];
     const Box b = seg_box<SEG, true>(b0, sg, i);
     const double wgt = weights ? weights[i] : 1.0;
-    for (int e = lane; e < a.KAt; e += 64)
-        dAs[e] = dEdA[(size_t)s * a.KAt + e] * wgt;
+    dpad_stage<NR>(dAs, dEdA + (size_t)s * a.KAt, a, wgt, lane, 64);
     const int c = cnt[i];
     const int *row = nbr + (size_t)i * cap;
     double *gs = g + (size_t)s * cap * 3;
@@ -666,21 +688,19 @@ __global__ void __launch_bounds__(256)
         const double r = sqrt(norm2_d(d)), ir = 1.0 / r;
         const double ux = d[0] * ir, uy = d[1] * ir, uz = d[2] * ir;
         double R[kMaxNrad], dR[kMaxNrad];
-        const int nrad = NR > 0 ? NR : a.nrad;
-        radial<double>(nrad, r, a.rc, R, dR);
-        const double *col = dAs + sp_clamp(species[j], a.ns) * nrad;
+        radial<double>(NR, r, a.rc, R, dR);
+        const double *col = dAs + sp_clamp(species[j], a.ns) * NR;
+        const int lm_stride = a.ns * NR;
         double rad = 0.0, vx = 0.0, vy = 0.0, vz = 0.0;
-        const int nchp = a.nchp;
         ylm_fixed<LM>(ux, uy, uz, Kn, [&](int lm, bool, double Y, double yx, double yy, double yz) {
             double sR = 0.0, sD = 0.0;
-            const double *cl = col + lm * nchp;
+            const double *cl = col + lm * lm_stride;
 #pragma unroll
-            for (int q = 0; q < (NR > 0 ? NR : kMaxNrad); ++q)
-                if (q < nrad) {
-                    const double v = cl[q];
-                    sR = fma_t(v, R[q], sR);
-                    sD = fma_t(v, dR[q], sD);
-                }
+            for (int q = 0; q < NR; ++q) {
+                const double v = cl[q];
+                sR = fma_t(v, R[q], sR);
+                sD = fma_t(v, dR[q], sD);
+            }
             rad = fma_t(sD, Y, rad);
             vx = fma_t(sR, yx, vx);
             vy = fma_t(sR, yy, vy);
@@ -719,17 +739,17 @@ __global__ void __launch_bounds__(256)
     const int s = s0 + half;
     const bool live = s < nS;
     extern __shared__ __align__(16) char smem_raw[];
-    // per wave: dE/dA rows of its two atoms, then the two pair lists
-    float *dAs = reinterpret_cast<float *>(smem_raw) + (size_t)w * (2 * a.KAt + 2 * cap);
-    int *lst = reinterpret_cast<int *>(dAs + 2 * a.KAt);
-    float *dA = dAs + half * a.KAt;
+    // per wave: padded dE/dA rows of its two atoms, then the two pair lists
+    const int row_len = a.L2 * a.ns * NR;
+    float *dAs = reinterpret_cast<float *>(smem_raw) + (size_t)w * (2 * row_len + 2 * cap);
+    int *lst = reinterpret_cast<int *>(dAs + 2 * row_len);
+    float *dA = dAs + half * row_len;
     int *pl = lst + half * cap;
     const int i = live ? S_idx[s] : 0;
     const Box b = seg_box<SEG, false>(b0, sg, i);
     const float wgt = (weights && live) ? float(weights[i]) : 1.0f;
     if (live)
-        for (int e = hl; e < a.KAt; e += 32)
-            dA[e] = dEdA[(size_t)s * a.KAt + e] * wgt;
+        dpad_stage<NR>(dA, dEdA + (size_t)s * a.KAt, a, wgt, hl, 32);
     const int c = live ? cnt[i] : 0;
     const int cmax = max(c, __shfl_xor(c, 32));
     const int *row = nbr + (size_t)i * cap;
@@ -776,21 +796,19 @@ __global__ void __launch_bounds__(256)
         const float r = float(rd);
         const float ux = float(d[0] * ird), uy = float(d[1] * ird), uz = float(d[2] * ird);
         float R[kMaxNrad], dR[kMaxNrad];
-        const int nrad = NR > 0 ? NR : a.nrad;
-        radial<float>(nrad, r, a.rc, R, dR);
-        const float *col = dA + sp_clamp(species[j], a.ns) * nrad;
+        radial<float>(NR, r, a.rc, R, dR);
+        const float *col = dA + sp_clamp(species[j], a.ns) * NR;
+        const int lm_stride = a.ns * NR;
         float rad = 0.f, vx = 0.f, vy = 0.f, vz = 0.f;
-        const int nchp = a.nchp;
         ylm_fixed<LM>(ux, uy, uz, Kn, [&](int lm, bool low, float Y, float yx, float yy, float yz) {
             float sR = 0.f, sD = 0.f;
-            const float *cl = col + lm * nchp;
+            const float *cl = col + lm * lm_stride;
 #pragma unroll
-            for (int q = 0; q < kMaxNrad; ++q)
-                if (q < nrad) {
-                    const float v = cl[q];
-                    sR += v * R[q];
-                    sD += v * dR[q];
-                }
+            for (int q = 0; q < NR; ++q) {
+                const float v = cl[q];
+                sR += v * R[q];
+                sD += v * dR[q];
+            }
             harmonic_adjoint(low, sR, sD, Y, yx, yy, yz, rad, vx, vy, vz);
         });
         const float ud = ux * vx + uy * vy + uz * vz;
@@ -1911,18 +1929,18 @@ static void finalize_t(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
             c.m.dp_stride, at<T>(ws, L.A), Dpart, at<T>(ws, L.dEdA), e_exp);
 }
 
-// f(integral_constant<radial functions>) for the counts compiled into the
-// vector pair adjoints (0: a guard per radial function)
+// f(integral_constant<padded radial functions>) for a model's count
 template <typename F>
 static void by_nrad(int nrad, F &&f)
 {
-    switch (nrad) {
+    switch (rules::padded_nrad(nrad)) {
+    case 4: f(std::integral_constant<int, 4>()); break;
     case 8: f(std::integral_constant<int, 8>()); break;
     case 12: f(std::integral_constant<int, 12>()); break;
-    case 16: f(std::integral_constant<int, 16>()); break;
-    default: f(std::integral_constant<int, 0>()); break;
+    default: f(std::integral_constant<int, 16>()); break;
     }
 }
+static_assert(kMaxNrad == 16, "by_nrad covers every padded count");
 
 // The vector pair adjoints: FP32 with two atoms per wave, FP64 with one.
 template <typename T>
@@ -1935,7 +1953,7 @@ static void pairgrad_t(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
         by_nrad(a.nrad, [&](auto nr) {
             constexpr int LM = decltype(lm)::value, NR = decltype(nr)::value;
             if constexpr (sizeof(T) == 4) {
-                const size_t sm = (size_t)4 * (2 * a.KAt + 2 * L.cap) * sizeof(float);
+                const size_t sm = (size_t)4 * (2 * a.L2 * a.ns * NR + 2 * L.cap) * sizeof(float);
                 auto kern = L.nseg > 0 ? k_ace_pairgrad_h<LM, NR, true> : k_ace_pairgrad_h<LM, NR, false>;
                 kern<<<(n + 7) / 8, 256, sm, s>>>(
                     pos, n, b, species, L.cap, at<int>(ws, L.nbr), at<int>(ws, L.cnt),
@@ -1943,7 +1961,7 @@ static void pairgrad_t(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
                     at<float>(ws, L.dEdA), weights, at<float>(ws, L.g), seg_args(ws, L), a.K);
             } else {
                 const int wpb = 4;
-                const size_t sm = (size_t)wpb * (a.KAt + ((L.cap + 3) & ~3) / 2) * sizeof(double);
+                const size_t sm = (size_t)wpb * (a.L2 * a.ns * NR + ((L.cap + 3) & ~3) / 2) * sizeof(double);
                 auto kern = L.nseg > 0 ? k_ace_pairgrad_d<LM, NR, true> : k_ace_pairgrad_d<LM, NR, false>;
                 kern<<<(n + wpb - 1) / wpb, 64 * wpb, sm, s>>>(
                     pos, n, b, species, L.cap, at<int>(ws, L.nbr), at<int>(ws, L.cnt),

@@ -1,0 +1,22 @@
+"""The library's dispatch rules (csrc/rules.h), compiled for the host: a small
+C wrapper around each, called through ctypes."""
+import ctypes
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SOURCE = """
+#include "rules.h"
+using namespace mlmix;
+extern "C" int padded_nrad(int n) { return rules::padded_nrad(n); }
+"""
+
+
+def load(folder):
+    src, lib = os.path.join(folder, "rules.cpp"), os.path.join(folder, "librules.so")
+    with open(src, "w") as f:
+        f.write(SOURCE)
+    csrc = os.path.join(ROOT, "paper_2502_19081_amd", "csrc")
+    subprocess.check_call(["g++", "-std=c++17", "-shared", "-fPIC", "-I", csrc, src, "-o", lib])
+    return ctypes.CDLL(lib)
