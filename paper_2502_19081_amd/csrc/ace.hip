@@ -1386,8 +1386,11 @@ struct PairWgLds {
     static_assert(4 * 64 * 4 <= P_ROWS, "partial sums fit the R rows");
 };
 
+// At one channel tile the LDS holds four workgroups per CU, so lmax 5 (132
+// registers by itself, 115 when bounded) is held to four waves per SIMD: all-
+// expensive FP32 call of 2,000 / 16,000 atoms, 16 functions: 170 -> 164 / 1,007 -> 960 us.
 template <int MT, int LM, bool SEG>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, MT == 1 && LM == 5 ? 4 : 1)
     k_ace_pairgrad_wg(const double *__restrict__ pos, int n, Box b0,
                       const int32_t *__restrict__ species, int cap, const int *__restrict__ nbr,
                       const int *__restrict__ cnt, const int *__restrict__ S_idx,

@@ -69,3 +69,12 @@ def test_vector_pair_adjoints(kernels, name, at_least):
     assert len(got) == 7 * 4 * 2  # lmax, padded radial counts, single or batched
     assert min(got.values()) >= at_least, got
     assert all(kernels[k][1] == 0 for k in got)
+
+
+# The workgroup pair adjoint at one channel tile: four, as many as its LDS
+# leaves room for.
+def test_workgroup_pair_adjoint(kernels):
+    got = _waves(kernels, r"k_ace_pairgrad_wgILi1E")
+    assert len(got) == 6 * 2  # lmax 0 .. 5, single or batched
+    assert min(got.values()) >= 4, got
+    assert all(kernels[k][1] == 0 for k in got)
