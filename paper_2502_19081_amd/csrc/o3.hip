@@ -40,6 +40,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "rules.h"
 
 namespace mlmix {
 
@@ -830,17 +831,65 @@ __device__ __forceinline__ void o3w_sparse(const float *__restrict__ At, int L2,
     }
 }
 
-// S atoms of species 0 without a neighbour of another species (class 1 of the
-// wide contraction) listed from the front of perm, the others from its end, both
-// in order; their number goes to the header. A neighbour shows in its species'
-// first channel of A_00: every term is the envelope (1 - (r/rc)^2)^2 > 0, and
-// where that rounds to zero so do the species' other channels. Every workgroup
-// counts the atoms before its own by itself (one launch), several loads of a
-// thread in flight.
+// Class 1 of the wide contraction: S atoms of species 0 without a neighbour of
+// another species. A neighbour shows in its species' first channel of A_00: every
+// term is the envelope (1 - (r/rc)^2)^2 > 0, and where that rounds to zero so do
+// the species' other channels.
+__device__ __forceinline__ bool o3_pure(int s, const int32_t *__restrict__ species,
+                                        const int *__restrict__ S_idx, const float *__restrict__ A,
+                                        int KAt, int nrad, int ns)
+{
+    bool p = sp_clamp(species[S_idx[s]], ns) == 0;
+    for (int z = 1; z < ns; ++z)
+        p = p && A[(size_t)s * KAt + z * nrad] == 0.0f;
+    return p;
+}
+
+// Sum over a workgroup of 1024 threads, on every thread.
+__device__ __forceinline__ int o3_block_sum(int v, int *part)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1)
+        v += __shfl_xor(v, d);
+    if (lane == 0)
+        part[w] = v;
+    __syncthreads();
+    int sum = 0;
+    for (int k = 0; k < 16; ++k)
+        sum += part[k];
+    __syncthreads();
+    return sum;
+}
+
+// Class-1 atoms of every 1024 S atoms, for k_o3_order.
+__global__ void __launch_bounds__(1024)
+    k_o3_count(const int *__restrict__ hdr, const int32_t *__restrict__ species,
+               const int *__restrict__ S_idx, const float *__restrict__ A, int KAt, int nrad, int ns,
+               int *__restrict__ counts)
+{
+    const int nS = hdr[H_NS];
+    const int b0 = blockIdx.x * 1024, s = b0 + threadIdx.x;
+    if (b0 >= nS)
+        return;  // uniform across the workgroup
+    __shared__ int part[16];
+    const int sum = o3_block_sum(s < nS && o3_pure(s, species, S_idx, A, KAt, nrad, ns) ? 1 : 0, part);
+    if (threadIdx.x == 0)
+        counts[blockIdx.x] = sum;
+}
+
+// The S atoms of class 1 listed from the front of perm, the others from its end,
+// both in order; the number of the first goes to the header. The atoms before a
+// workgroup's own are counted by k_o3_count (CNT), or in a short list by the
+// workgroup itself, several loads of a thread in flight, which saves that launch
+// but grows with the square of |S|: all-expensive calls of a light two-species
+// model, counted by themselves / by k_o3_count: 20.9 / 14.1 ms on 1,024,000
+// atoms, 7.90 / 6.94 on 524,288.
+template <bool CNT>
 __global__ void __launch_bounds__(1024)
     k_o3_order(int *__restrict__ hdr, const int32_t *__restrict__ species,
                const int *__restrict__ S_idx, const float *__restrict__ A, int KAt, int nrad, int ns,
-               int scap, int *__restrict__ perm)
+               int scap, const int *__restrict__ counts, int *__restrict__ perm)
 {
     const int nS = hdr[H_NS];
     const int b0 = blockIdx.x * 1024;
@@ -848,28 +897,18 @@ __global__ void __launch_bounds__(1024)
         return;  // uniform across the workgroup
     __shared__ int part[16];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    auto pure = [&](int s) {
-        bool p = sp_clamp(species[S_idx[s]], ns) == 0;
-        for (int z = 1; z < ns; ++z)
-            p = p && A[(size_t)s * KAt + z * nrad] == 0.0f;
-        return p;
-    };
     int cnt = 0;
+    if constexpr (CNT) {
+        for (int k = tid; k < (int)blockIdx.x; k += 1024)
+            cnt += counts[k];
+    } else {
 #pragma unroll 8
-    for (int s = tid; s < b0; s += 1024)
-        cnt += pure(s) ? 1 : 0;
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1)
-        cnt += __shfl_xor(cnt, d);
-    if (lane == 0)
-        part[w] = cnt;
-    __syncthreads();
-    int before = 0;  // class-1 atoms before this workgroup's
-    for (int k = 0; k < 16; ++k)
-        before += part[k];
-    __syncthreads();
+        for (int s = tid; s < b0; s += 1024)
+            cnt += o3_pure(s, species, S_idx, A, KAt, nrad, ns) ? 1 : 0;
+    }
+    const int before = o3_block_sum(cnt, part);  // class-1 atoms before this workgroup's
     const int s = b0 + tid;
-    const bool on = s < nS && pure(s);
+    const bool on = s < nS && o3_pure(s, species, S_idx, A, KAt, nrad, ns);
     const unsigned long long msk = __ballot(on);
     if (lane == 0)
         part[w] = __popcll(msk);
@@ -1271,9 +1310,11 @@ void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
     a.ns = m.ns;
     a.nrad = m.nrad;
     a.scap = L.scap;
-    // the class lists sit in the pair gradients, which the pair adjoint of the
-    // same evaluation (or of a later backward) writes before anything reads them
-    a.perm = at<int>(ws, L.g);
+    // the class lists (and the counts behind them) sit in the pair gradients, which
+    // the pair adjoint of the same evaluation (or of a later backward) writes before
+    // anything reads them: 3 cap floats per S atom, at least scap + blocks here
+    int *perm = at<int>(ws, L.g), *counts = perm + L.scap;
+    a.perm = perm;
     const bool classes = m.ns > 1 && L.scap > 0 && L.cap >= 1;
     // K order of a channel a's values b < n_rad: the full steps take b = NJ q + j
     // step by step (j), lane group by lane group (q)
@@ -1310,12 +1351,20 @@ void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
             return;
         }
         const int blocks = (L.scap + 1023) / 1024;
-        if (ev0)
-            hipExtLaunchKernelGGL(k_o3_order, dim3(blocks), dim3(1024), 0u, s, ev0, nullptr, 0u, hdr, species,
-                                  S_idx, A, m.KAt, m.nrad, m.ns, L.scap, const_cast<int *>(a.perm));
-        else
-            k_o3_order<<<blocks, 1024, 0, s>>>(hdr, species, S_idx, A, m.KAt, m.nrad, m.ns, L.scap,
-                                               const_cast<int *>(a.perm));
+        auto list = [&](auto kern, bool first, auto... rest) {
+            if (ev0)
+                hipExtLaunchKernelGGL(kern, dim3(blocks), dim3(1024), 0u, s, first ? ev0 : nullptr, nullptr, 0u,
+                                      hdr, species, S_idx, A, m.KAt, m.nrad, m.ns, rest...);
+            else
+                kern<<<blocks, 1024, 0, s>>>(hdr, species, S_idx, A, m.KAt, m.nrad, m.ns, rest...);
+        };
+        // (a capacity of up to 16,384 takes the single launch)
+        if (rules::o3_count_first(L.scap)) {
+            list(k_o3_count, true, counts);
+            list(k_o3_order<true>, false, L.scap, counts, perm);
+        } else {
+            list(k_o3_order<false>, true, L.scap, counts, perm);
+        }
         go(k_ace_o3w<QM, NC, 2>, false, false, false);  // the long tiles first
         go(k_ace_o3w<QM, NC, 1>, true, false, true);
     });

@@ -9,5 +9,10 @@ namespace rules {
 // count (1 .. 16) rounded up to a multiple of four, as the channels are.
 constexpr int padded_nrad(int nrad) { return (nrad + 3) & ~3; }
 
+// Class lists of the wide contraction: count the workgroups' atoms in a launch of
+// its own above this S capacity. Below, each of at most 16 workgroups counts at
+// most 15 rounds of atoms itself, which costs what the launch would.
+constexpr bool o3_count_first(int scap) { return scap > 16384; }
+
 }  // namespace rules
 }  // namespace mlmix

@@ -10,6 +10,7 @@ SOURCE = """
 #include "rules.h"
 using namespace mlmix;
 extern "C" int padded_nrad(int n) { return rules::padded_nrad(n); }
+extern "C" int o3_count_first(int scap) { return rules::o3_count_first(scap); }
 """
 
 

@@ -1,0 +1,75 @@
+"""The class lists of the wide order-3 contraction over several workgroups of
+1024 S atoms: |S| on both sides of the workgroup's size, lists ranked by their
+own counts (capacities up to 16,384) and by counts of a launch before (above),
+and a second round of tiles per workgroup. About one atom in a hundred is of
+the second species, so both classes hold atoms of every workgroup.
+
+Tolerance against the oracle: FP32 rounds at 6e-8; a force sums up to about 1e4
+products (two and six channels, lmax 1), so independent roundings leave 6e-8 x
+1e2 = 6e-6 of the sum of magnitudes; 3e-5 of the largest force. The two ways
+of listing give the same order and so the same bits.
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+from gen import workloads as W
+from tests.gpu_common import rel_force_err, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _cell(cells, n_rad, lmax, seed=61):
+    w = W.tiny(seed=seed, cells=cells, n_rad=n_rad, lmax=lmax)
+    r = W._streams(seed + 1)
+    w["model"]["n_species"] = 2
+    w["model"]["ace"] = W.ace_params(r[1], 2, n_rad, lmax, 3, 4.2, W.ACE_SCALE["tiny"])
+    w["model"]["uf3"] = W.uf3_params(r[2], 2, 8, 4.2, 0, 3.2)
+    w["species"] = (np.random.default_rng(6).random(len(w["pos"])) < 0.01).astype(np.int32)
+    return w
+
+
+def _with_s(w, n_s):
+    """A sphere that holds n_s atoms, without a buffer."""
+    d = w["pos"] - w["L"] / 2
+    d -= w["L"] * np.round(d / w["L"])
+    r = np.sort(np.linalg.norm(d, axis=1))
+    w["regions"] = [W.sphere(w["L"] / 2, 0.5 * (r[n_s - 1] + r[n_s]) - 0.3, 0.3)]
+    w["r_buffer"] = 0.0
+    return w
+
+
+def _check(w, mode, s_cap=0, ref=None):
+    from paper_2502_19081_amd import core
+    model = core.Model(w["model"], precision="fp32")
+    _, sy, pos, sp = core.system_for(w, model=model, s_cap=s_cap)
+    g = run_gpu(w, mode, system=(sy, pos, sp))
+    if ref is not None:
+        assert np.array_equal(g["S"], ref["S"])
+        assert rel_force_err(g["forces"], ref["forces"]) < 3e-5
+        assert np.abs(g["e_exp"] - ref["e_exp"]).max() < 3e-5 * max(1.0, np.abs(ref["e_exp"]).max())
+    return g
+
+
+@pytest.mark.parametrize("n_s", [1023, 1024, 1025, 2049, 3100])
+def test_several_workgroups(n_s):
+    w = _with_s(_cell(12, 6, 1), n_s)
+    print(f"|S| {n_s}", flush=True)
+    ref = O.mixed(w, O.MODE_MIXED)
+    assert len(_check(w, O.MODE_MIXED, ref=ref)["S"]) == n_s
+
+
+def test_both_ways_of_listing():
+    w = _with_s(_cell(21, 4, 1), 3100)  # 18,522 atoms
+    print("|S| 3100, capacities 18,522 and 4,000", flush=True)
+    ref = O.mixed(w, O.MODE_MIXED)
+    counted, alone = _check(w, O.MODE_MIXED, ref=ref), _check(w, O.MODE_MIXED, s_cap=4000)
+    for k in ("forces", "e_exp"):
+        assert np.array_equal(counted[k], alone[k]), k
+
+
+def test_above_the_single_launch():
+    w = _cell(21, 2, 1)
+    print("|S| 18,522", flush=True)
+    ref = O.mixed(w, O.MODE_ALL_EXPENSIVE)
+    assert len(_check(w, O.MODE_ALL_EXPENSIVE, ref=ref)["S"]) == len(w["pos"])

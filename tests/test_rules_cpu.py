@@ -26,3 +26,12 @@ def test_padded_radial_counts_and_their_lds(lib):
                 assert 4 * (2 * rows + 2 * cap) * 4 <= 65536    # FP32: eight rows and lists
                 inv = (65536 + ns - 1) // ns
                 assert all((r * inv) >> 16 == r // ns for r in range(l2 * ns))
+
+
+def test_class_lists_count_before_they_rank_in_large_capacities(lib):
+    # a workgroup that counts the atoms before its own reads at most 15 others' share
+    for scap in (1, 1024, 16384, 16385, 65536, 1024000):
+        blocks = (scap + 1023) // 1024
+        assert lib.o3_count_first(scap) == (blocks > 16)
+        # the lists and the counts fit the pair gradients, three floats a slot
+        assert scap + blocks <= 3 * scap
