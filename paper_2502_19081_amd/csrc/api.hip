@@ -16,6 +16,7 @@
 
 #include "basis.h"
 #include "internal.h"
+#include "rules.h"
 
 using namespace mlmix;
 
@@ -1486,8 +1487,11 @@ try {
     if (const char *e = std::getenv("MLMIX_O3_MAX_SPLIT")) {
         int v = std::atoi(e);
         if (v == 1 || v == 2 || v == 4 || v == 8 || v == 16)
-            c.o3_max_split = v;
+            c.o3_max_split = c.o3_class_split = v;
     }
+    c.o3_classes = rules::o3_classes(d.n_species, nch, ctx->flops[0]);
+    if (const char *e = std::getenv("MLMIX_O3_CLASSES"))
+        c.o3_classes = d.n_species > 1 && std::atoi(e);  // 0 one class, 1 two (comparisons)
     if (const char *e = std::getenv("MLMIX_FUSE_FIN"))
         c.fuse_fin = std::atoi(e) ? 1 : 0;  // 0: the finalisation as its own kernel (comparisons)
     if (const char *e = std::getenv("MLMIX_O3_VALU"))
@@ -1783,6 +1787,9 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
         {
             StageTimer t(ctx, s, ST_BASIS);
             launch_ace_basis(s, c, ws, L, b, pos, species);
+            // before the fork: beside the cheap potential each of these short
+            // launches would wait for compute units
+            launch_ace_lists(s, c, ws, L, species);
         }
         if (late) {
             int rc = record_fork();
@@ -1792,7 +1799,7 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
         {
             // the matrix-core contraction is one kernel: timed by its own events
             StageTimer t(ctx, s, ST_CONTRACT, c.o3 && c.prec != MLMIX_FP64);
-            launch_ace_contract(s, c, ws, L, species, t.k0, t.k1);
+            launch_ace_contract(s, c, ws, L, species, t.k0, t.k1, true);
         }
         if (late) {
             int rc = fork_side();

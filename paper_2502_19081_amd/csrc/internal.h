@@ -247,6 +247,8 @@ struct Ctx {
     // 16.7 / 18.3 / 18.2 us with eight; on 102,858 atoms in S 3.32 ms with
     // four waves and 3.42 with eight
     int o3_max_split = 4;
+    bool o3_classes = false;            // wide form: S atoms in two classes (rules.h)
+    int o3_class_split = kO3MaxSplit;   // largest split of a class's tiles
     int o3_waves = 8;      // waves per workgroup of the single-species form (4 or 8)
     int o3v = 1;           // FP32 single-species form with the vector sparse stage
     int fuse_fin = 1;      // the matrix-core pair adjoint does the finalisation
@@ -311,7 +313,9 @@ void launch_ace_basis(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, 
 // kernel (hipExtLaunchKernel), for stage timing
 void launch_ace_contract(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
                          const int32_t *species, hipEvent_t ev0 = nullptr,
-                         hipEvent_t ev1 = nullptr);
+                         hipEvent_t ev1 = nullptr, bool listed = false);
+// class lists of the wide contraction, for a contraction called with listed
+void launch_ace_lists(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, const int32_t *species);
 void launch_ace_finalize(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
                          const int32_t *species, double *e_exp);
 // e_exp: where the pair adjoint writes the site energies when it does the
@@ -329,7 +333,8 @@ size_t o3v_lds_bytes(const Ctx &c);
 int o3v_waves(const Ctx &c, int n);
 int o3v_grid(const Ctx &c, int n);
 void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
-                    const int32_t *species, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                    const int32_t *species, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
+                    bool listed = false);
 size_t o3w_lds_bytes(const Ctx &c);
 hipError_t o3w_prepare(const Ctx &c);
 void launch_ace_o3d(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L);

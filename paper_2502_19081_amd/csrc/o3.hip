@@ -796,6 +796,7 @@ struct O3WArgs {
     const int *wbeg;
     const int *dp_off;  // per-block offset in the partial buffer
     int n_pb, nch, L2, KAt, dp_stride, max_split, ns;
+    int fill_split;     // splits up to this fill the grid, further ones only fit it
     int np, nstm;       // BF16: passes of eight channels a, steps per pass at most
     int nrad, scap;
     const int *perm;    // CLS 1, 2: S atoms by class, from the front and from the end
@@ -943,13 +944,7 @@ __global__ void __launch_bounds__(256, CLS == 1 ? 2 : 1)
     const int nS = hdr[H_NS];
     const int nC = CLS == 0 ? nS : (CLS == 1 ? hdr[H_O3PURE] : nS - hdr[H_O3PURE]);
     const int ntile = (nC + kO3Atoms - 1) / kO3Atoms;
-    int G = 1, lg = 0;
-    // CLS 2 holds few atoms, one workgroup per CU: no second round
-    while (G < (CLS == 0 ? a.max_split : kO3MaxSplit) &&
-           (CLS == 2 ? 2 * ntile * G <= (int)gridDim.x : ntile * G < (int)gridDim.x)) {
-        G <<= 1;
-        ++lg;
-    }
+    const int lg = rules::o3_split_log(ntile, (int)gridDim.x, a.max_split, a.fill_split), G = 1 << lg;
     const int nitem = ntile * G;
     // the splits of one tile on one XCD: its A rows come from that XCD's L2
     // after the first fetch
@@ -1285,8 +1280,44 @@ hipError_t o3w_prepare(const Ctx &c)
     });
 }
 
+// The class lists (and the counts behind them) sit in the pair gradients, which the
+// pair adjoint of the same evaluation (or of a later backward) writes before
+// anything reads them: 3 cap floats per S atom, at least scap + blocks here.
+static int *o3w_perm(void *ws, const WsLayout &L) { return at<int>(ws, L.g); }
+
+static void o3w_lists(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, const int32_t *species,
+                      hipEvent_t ev0)
+{
+    const DevModel &m = c.m;
+    int *perm = o3w_perm(ws, L), *counts = perm + L.scap;
+    const int blocks = (L.scap + 1023) / 1024;
+    auto go = [&](auto kern, bool first, auto... rest) {
+        if (ev0)
+            hipExtLaunchKernelGGL(kern, dim3(blocks), dim3(1024), 0u, s, first ? ev0 : nullptr, nullptr, 0u,
+                                  at<int>(ws, L.hdr), species, at<int>(ws, L.S_idx), at<float>(ws, L.A), m.KAt,
+                                  m.nrad, m.ns, rest...);
+        else
+            kern<<<blocks, 1024, 0, s>>>(at<int>(ws, L.hdr), species, at<int>(ws, L.S_idx), at<float>(ws, L.A),
+                                         m.KAt, m.nrad, m.ns, rest...);
+    };
+    if (rules::o3_count_first(L.scap)) {
+        go(k_o3_count, true, counts);
+        go(k_o3_order<true>, false, L.scap, counts, perm);
+    } else {
+        go(k_o3_order<false>, true, L.scap, counts, perm);
+    }
+}
+
+static bool o3w_classes(const Ctx &c, const WsLayout &L) { return c.o3_classes && L.scap > 0; }
+
+void launch_ace_lists(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, const int32_t *species)
+{
+    if (L.n > 0 && c.prec != MLMIX_FP64 && c.o3 == 2 && o3w_classes(c, L))
+        o3w_lists(s, c, ws, L, species, nullptr);
+}
+
 void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
-                    const int32_t *species, hipEvent_t ev0, hipEvent_t ev1)
+                    const int32_t *species, hipEvent_t ev0, hipEvent_t ev1, bool listed)
 {
     const DevModel &m = c.m;
     const char *base = static_cast<const char *>(m.base);
@@ -1306,16 +1337,12 @@ void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
     a.L2 = m.L2;
     a.KAt = m.KAt;
     a.dp_stride = m.dp_stride;
-    a.max_split = c.o3_max_split;
     a.ns = m.ns;
     a.nrad = m.nrad;
     a.scap = L.scap;
-    // the class lists (and the counts behind them) sit in the pair gradients, which
-    // the pair adjoint of the same evaluation (or of a later backward) writes before
-    // anything reads them: 3 cap floats per S atom, at least scap + blocks here
-    int *perm = at<int>(ws, L.g), *counts = perm + L.scap;
-    a.perm = perm;
-    const bool classes = m.ns > 1 && L.scap > 0 && L.cap >= 1;
+    a.perm = o3w_perm(ws, L);
+    const bool classes = o3w_classes(c, L);
+    a.max_split = classes ? c.o3_class_split : c.o3_max_split;
     // K order of a channel a's values b < n_rad: the full steps take b = NJ q + j
     // step by step (j), lane group by lane group (q)
     {
@@ -1339,6 +1366,11 @@ void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
         auto go = [&](auto kern, bool one, bool first, bool last) {
             const size_t lds = o3w_lds(c, one);
             const int per_cu = lds <= 80 * 1024 ? 2 : 1;
+            // class 2, few tiles as a rule and with most of the work, takes no second
+            // round of workgroups for a split: at all where one of them fills a CU's
+            // LDS, beyond the general split where two share it (an alloy, all of it
+            // class 2, then runs as one class does)
+            a.fill_split = !classes || one ? a.max_split : (per_cu == 1 ? 1 : c.o3_max_split);
             const int grid = (int)std::min<long>(std::max<long>(items, 1), 256L * per_cu);
             if (ev0)
                 hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), (uint32_t)lds, s, first ? ev0 : nullptr,
@@ -1350,22 +1382,9 @@ void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
             go(k_ace_o3w<QM, NC, 0>, false, true, true);
             return;
         }
-        const int blocks = (L.scap + 1023) / 1024;
-        auto list = [&](auto kern, bool first, auto... rest) {
-            if (ev0)
-                hipExtLaunchKernelGGL(kern, dim3(blocks), dim3(1024), 0u, s, first ? ev0 : nullptr, nullptr, 0u,
-                                      hdr, species, S_idx, A, m.KAt, m.nrad, m.ns, rest...);
-            else
-                kern<<<blocks, 1024, 0, s>>>(hdr, species, S_idx, A, m.KAt, m.nrad, m.ns, rest...);
-        };
-        // (a capacity of up to 16,384 takes the single launch)
-        if (rules::o3_count_first(L.scap)) {
-            list(k_o3_count, true, counts);
-            list(k_o3_order<true>, false, L.scap, counts, perm);
-        } else {
-            list(k_o3_order<false>, true, L.scap, counts, perm);
-        }
-        go(k_ace_o3w<QM, NC, 2>, false, false, false);  // the long tiles first
+        if (!listed)
+            o3w_lists(s, c, ws, L, species, ev0);
+        go(k_ace_o3w<QM, NC, 2>, false, listed, false);  // the long tiles first
         go(k_ace_o3w<QM, NC, 1>, true, false, true);
     });
 }

@@ -1,7 +1,7 @@
 """The class lists of the wide order-3 contraction over several workgroups of
 1024 S atoms: |S| on both sides of the workgroup's size, lists ranked by their
-own counts (capacities up to 16,384) and by counts of a launch before (above),
-and a second round of tiles per workgroup. About one atom in a hundred is of
+own counts (capacities up to 65,536) and by counts of a launch before (above),
+and more tiles than workgroups. About one atom in a hundred is of
 the second species, so both classes hold atoms of every workgroup.
 
 Tolerance against the oracle: FP32 rounds at 6e-8; a force sums up to about 1e4
@@ -17,6 +17,12 @@ from gen import workloads as W
 from tests.gpu_common import rel_force_err, run_gpu
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _two_classes(monkeypatch):
+    """Light models, which would run as one class, in two."""
+    monkeypatch.setenv("MLMIX_O3_CLASSES", "1")
 
 
 def _cell(cells, n_rad, lmax, seed=61):
@@ -60,8 +66,8 @@ def test_several_workgroups(n_s):
 
 
 def test_both_ways_of_listing():
-    w = _with_s(_cell(21, 4, 1), 3100)  # 18,522 atoms
-    print("|S| 3100, capacities 18,522 and 4,000", flush=True)
+    w = _with_s(_cell(33, 4, 1), 3100)  # 71,874 atoms
+    print("|S| 3100, capacities 71,874 and 4,000", flush=True)
     ref = O.mixed(w, O.MODE_MIXED)
     counted, alone = _check(w, O.MODE_MIXED, ref=ref), _check(w, O.MODE_MIXED, s_cap=4000)
     for k in ("forces", "e_exp"):
@@ -69,7 +75,46 @@ def test_both_ways_of_listing():
 
 
 def test_above_the_single_launch():
-    w = _cell(21, 2, 1)
-    print("|S| 18,522", flush=True)
+    w = _cell(33, 2, 1)
+    print("|S| 71,874", flush=True)
     ref = O.mixed(w, O.MODE_ALL_EXPENSIVE)
     assert len(_check(w, O.MODE_ALL_EXPENSIVE, ref=ref)["S"]) == len(w["pos"])
+
+
+def _widths(species_of, ns, n_rad, lmax):
+    w = W.tiny(seed=71, cells=4, n_rad=n_rad, lmax=lmax)
+    r = W._streams(72)
+    w["model"]["n_species"] = ns
+    w["model"]["ace"] = W.ace_params(r[1], ns, n_rad, lmax, 3, 4.2, W.ACE_SCALE["tiny"])
+    w["model"]["uf3"] = W.uf3_params(r[2], ns, 8, 4.2, 0, 3.2)
+    g = np.random.default_rng(7)
+    n = len(w["pos"])
+    w["species"] = {"dilute": (g.random(n) < 0.02).astype(np.int32), "first": np.zeros(n, np.int32),
+                    "second": np.ones(n, np.int32),
+                    "alloy": g.integers(0, ns, n).astype(np.int32)}[species_of]
+    return w
+
+
+# One class and two give the same bits, whatever the width and the format of the
+# operands, and with every split of a tile; and the order-3 term is in them: without
+# it nearly every force has other bits.
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("species_of", ["dilute", "first", "second", "alloy"])
+@pytest.mark.parametrize("ns,n_rad,lmax", [(2, 1, 2), (2, 3, 3), (2, 6, 2), (2, 7, 3), (3, 5, 2), (2, 9, 3),
+                                           (2, 12, 2), (2, 14, 1), (3, 10, 1), (2, 16, 2), (4, 8, 1)])
+def test_one_class_and_two(monkeypatch, prec, species_of, ns, n_rad, lmax):
+    w = _widths(species_of, ns, n_rad, lmax)
+    print(f"{prec} {species_of} {ns} x {n_rad}, lmax {lmax}", flush=True)
+
+    def run(classes, split=None):
+        monkeypatch.setenv("MLMIX_O3_CLASSES", classes)
+        if split:
+            monkeypatch.setenv("MLMIX_O3_MAX_SPLIT", split)
+        return run_gpu(w, O.MODE_ALL_EXPENSIVE, precision=prec)
+
+    one = run("0")
+    for got in (run("1"), run("1", "1"), run("1", "2")):
+        for k in ("forces", "e_exp"):
+            assert np.array_equal(one[k], got[k]), k
+    w["model"]["ace"]["c3"] = np.zeros_like(w["model"]["ace"]["c3"])
+    assert (run("1")["forces"] != one["forces"]).mean() > 0.9

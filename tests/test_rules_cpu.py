@@ -29,9 +29,29 @@ def test_padded_radial_counts_and_their_lds(lib):
 
 
 def test_class_lists_count_before_they_rank_in_large_capacities(lib):
-    # a workgroup that counts the atoms before its own reads at most 15 others' share
-    for scap in (1, 1024, 16384, 16385, 65536, 1024000):
+    # a workgroup that counts the atoms before its own reads at most 63 others' share
+    for scap in (1, 1024, 16384, 65536, 65537, 1024000):
         blocks = (scap + 1023) // 1024
-        assert lib.o3_count_first(scap) == (blocks > 16)
+        assert lib.o3_count_first(scap) == (blocks > 64)
         # the lists and the counts fit the pair gradients, three floats a slot
         assert scap + blocks <= 3 * scap
+
+
+def test_classes_only_for_several_species_and_contractions_that_pay_for_them(lib):
+    for flops in (0.0, 1e5, 4e5, 6e5, 5e6):
+        assert not lib.o3_classes(1, 16, flops)
+        assert lib.o3_classes(2, 16, flops) == (flops >= 5e5)
+        assert lib.o3_classes(2, 20, flops) == (flops >= 3e5)
+
+
+@pytest.mark.parametrize("most", [1, 2, 4, 8, 16])
+def test_splits_of_a_tile(lib, most):
+    for grid in (16, 48, 256, 512):
+        for ntile in (0, 1, 3, 15, 16, 31, 100, 255, 256, 257, 500, 512, 513, 9000):
+            for fill in (1, 4, most):
+                g = 1 << lib.o3_split_log(ntile, grid, most, fill)
+                assert 1 <= g <= max(most, 1)
+                if g > fill:  # one round of workgroups
+                    assert ntile * g <= grid
+                if g < most:  # no further split would still help
+                    assert ntile * g * 2 > grid and (g >= fill or ntile * g >= grid)
