@@ -1988,7 +1988,7 @@ void launch_ace_basis(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, 
 }
 
 void launch_ace_contract(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
-                         const int32_t *species, hipEvent_t ev0, hipEvent_t ev1, bool listed)
+                         const int32_t *species, hipEvent_t ev0, hipEvent_t ev1)
 {
     if (L.n == 0) {
         if (ev0) {  // keep the stage's event pair complete
@@ -1999,7 +1999,7 @@ void launch_ace_contract(hipStream_t s, const Ctx &c, void *ws, const WsLayout &
     }
     if (c.prec != MLMIX_FP64 && c.o3) {
         if (c.o3 == 2)
-            launch_ace_o3w(s, c, ws, L, species, ev0, ev1, listed);
+            launch_ace_o3w(s, c, ws, L, species, ev0, ev1);
         else
             launch_ace_o3(s, c, ws, L, ev0, ev1);
         return;

@@ -1487,7 +1487,7 @@ try {
     if (const char *e = std::getenv("MLMIX_O3_MAX_SPLIT")) {
         int v = std::atoi(e);
         if (v == 1 || v == 2 || v == 4 || v == 8 || v == 16)
-            c.o3_max_split = c.o3_class_split = v;
+            c.o3_max_split = c.o3_wide_split = v;
     }
     c.o3_classes = rules::o3_classes(d.n_species, nch, ctx->flops[0]);
     if (const char *e = std::getenv("MLMIX_O3_CLASSES"))
@@ -1524,6 +1524,8 @@ try {
         (void)hipGetLastError();
         c.o3 = 0;
     }
+    if (c.o3)
+        c.o3_weight = rules::o3_weight(c.o3, c.qmode != 0, c.o3_classes, ctx->flops[0] - ctx->flops[5], ctx->flops[5]);
     if ((c.qmode == 2 && c.o3 != 1) || (c.qmode == 1 && c.o3 == 0)) {
         return fail(MLMIX_E_ARG, "the FP8 contraction mode needs a single-species model with at "
                                  "most 16 channels, the BF16 mode a model of at most 32 channels "
@@ -1749,7 +1751,11 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
     // 1: recorded after the atomic basis, issued after the contraction
     // With the cheap potential masked its kernel needs the final masks: the
     // fork point then follows the region stage.
-    const int fork_at = c.fork_at >= 0 ? c.fork_at : (c.o3 && L.nseg == 0 && !capturing ? 1 : 2);
+    const int fork_at = c.fork_at >= 0 ? c.fork_at
+                        : L.nseg == 0 && !capturing &&
+                                rules::fork_after_basis(c.o3_weight, L.n, (mode & MLMIX_FORCE_REBUILD) != 0)
+                            ? 1
+                            : 2;
     const bool late = fork_at == 1 && m != MLMIX_MODE_ALL_CHEAP && !masked;
     if (fork_at == 2 && !masked) {
         int rc = record_fork();
@@ -1787,9 +1793,6 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
         {
             StageTimer t(ctx, s, ST_BASIS);
             launch_ace_basis(s, c, ws, L, b, pos, species);
-            // before the fork: beside the cheap potential each of these short
-            // launches would wait for compute units
-            launch_ace_lists(s, c, ws, L, species);
         }
         if (late) {
             int rc = record_fork();
@@ -1799,7 +1802,7 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
         {
             // the matrix-core contraction is one kernel: timed by its own events
             StageTimer t(ctx, s, ST_CONTRACT, c.o3 && c.prec != MLMIX_FP64);
-            launch_ace_contract(s, c, ws, L, species, t.k0, t.k1, true);
+            launch_ace_contract(s, c, ws, L, species, t.k0, t.k1);
         }
         if (late) {
             int rc = fork_side();

@@ -215,25 +215,15 @@ struct Ctx {
     int basis_mfma = 1;    // atomic basis and pair adjoint on the matrix cores (FP32)
     int basis_chunks = -1; // basis in 64-slot passes: -1 above 65,536 atoms, 0 never, 1 always
     // second-stream fork after the rows (0), recorded after the basis (1), or recorded
-    // after the rows and issued after the compaction (2); -1 automatic: 1 for a
-    // single system whose order-3 contraction runs on the matrix cores and whose
-    // steps are not captured, else 2.
-    // The cheap potential's workgroups (one wave per atom, all at once) keep
-    // the few blocks of the compaction and the basis waiting when they start
-    // first, while the contraction's occupy the compute units for long enough
-    // to hide the cheap potential behind them. Per call of 20 steps, 2 against
-    // 1: 1,930 / 1,830 us at 8,191 atoms and 1,668 / 1,555 at 1,457 (one
-    // defect, FP32), 2,800 / 2,560 (FP64, 8,191); per 4 steps at 249,960 atoms
-    // with 40 defects (BF16) 7,245 / 6,720, at 1,023,800 with 200 (FP32) 37.3 /
-    // 36.1 ms. Without an order-3 contraction the chain after the basis is too
-    // short: 1,680 / 1,910 us at 21,295 atoms. A batch of 16 systems: 4,930 /
-    // 5,030 us per 5 steps (its contraction is two launches of few workgroups).
-    // Captured, the early fork wins: 88 / 99 us per step on 8,193 atoms and 6.88 /
-    // 7.57 ms on 1,023,800, 2 against 1.
+    // after the rows and issued after the compaction (2); -1 automatic: 1 where
+    // rules::fork_after_basis says so, for single systems whose steps are not
+    // captured, else 2. A batch of 16 systems: 4,930 / 5,030 us per 5 steps, 2 against
+    // 1 (its contraction is two launches of few workgroups). Captured, the early fork
+    // wins: 88 / 99 us per step on 8,193 atoms and 6.88 / 7.57 ms on 1,023,800.
     // At 1 the event is recorded after the basis and the side kernels are issued
-    // after the contraction: a caller that makes one call per step waits on the
-    // host's launches (issued before it 76 M, after it 80 M atom-steps/s at 8,193).
+    // after the contraction, so that the host's launches of the main chain go first.
     int fork_at = -1;
+    double o3_weight = 0.0;  // of the contraction, for that rule (0: none on the matrix cores)
     // workgroup cap of the cheap-potential kernel on the second stream
     // (grid-stride loop): -1 automatic, 0 uncapped. Automatic: uncapped (caps
     // of 1,280 to 4,096 workgroups measured no better on 8,191 atoms and 3-12 %
@@ -248,7 +238,7 @@ struct Ctx {
     // four waves and 3.42 with eight
     int o3_max_split = 4;
     bool o3_classes = false;            // wide form: S atoms in two classes (rules.h)
-    int o3_class_split = kO3MaxSplit;   // largest split of a class's tiles
+    int o3_wide_split = kO3MaxSplit;    // largest split of its tiles
     int o3_waves = 8;      // waves per workgroup of the single-species form (4 or 8)
     int o3v = 1;           // FP32 single-species form with the vector sparse stage
     int fuse_fin = 1;      // the matrix-core pair adjoint does the finalisation
@@ -313,9 +303,7 @@ void launch_ace_basis(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, 
 // kernel (hipExtLaunchKernel), for stage timing
 void launch_ace_contract(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
                          const int32_t *species, hipEvent_t ev0 = nullptr,
-                         hipEvent_t ev1 = nullptr, bool listed = false);
-// class lists of the wide contraction, for a contraction called with listed
-void launch_ace_lists(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, const int32_t *species);
+                         hipEvent_t ev1 = nullptr);
 void launch_ace_finalize(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
                          const int32_t *species, double *e_exp);
 // e_exp: where the pair adjoint writes the site energies when it does the
@@ -333,8 +321,7 @@ size_t o3v_lds_bytes(const Ctx &c);
 int o3v_waves(const Ctx &c, int n);
 int o3v_grid(const Ctx &c, int n);
 void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
-                    const int32_t *species, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
-                    bool listed = false);
+                    const int32_t *species, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 size_t o3w_lds_bytes(const Ctx &c);
 hipError_t o3w_prepare(const Ctx &c);
 void launch_ace_o3d(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L);

@@ -796,7 +796,7 @@ struct O3WArgs {
     const int *wbeg;
     const int *dp_off;  // per-block offset in the partial buffer
     int n_pb, nch, L2, KAt, dp_stride, max_split, ns;
-    int fill_split;     // splits up to this fill the grid, further ones only fit it
+    bool fill;          // split to fill the grid, else to one round of it
     int np, nstm;       // BF16: passes of eight channels a, steps per pass at most
     int nrad, scap;
     const int *perm;    // CLS 1, 2: S atoms by class, from the front and from the end
@@ -863,68 +863,53 @@ __device__ __forceinline__ int o3_block_sum(int v, int *part)
     return sum;
 }
 
-// Class-1 atoms of every 1024 S atoms, for k_o3_order.
-__global__ void __launch_bounds__(1024)
-    k_o3_count(const int *__restrict__ hdr, const int32_t *__restrict__ species,
-               const int *__restrict__ S_idx, const float *__restrict__ A, int KAt, int nrad, int ns,
-               int *__restrict__ counts)
-{
-    const int nS = hdr[H_NS];
-    const int b0 = blockIdx.x * 1024, s = b0 + threadIdx.x;
-    if (b0 >= nS)
-        return;  // uniform across the workgroup
-    __shared__ int part[16];
-    const int sum = o3_block_sum(s < nS && o3_pure(s, species, S_idx, A, KAt, nrad, ns) ? 1 : 0, part);
-    if (threadIdx.x == 0)
-        counts[blockIdx.x] = sum;
-}
-
 // The S atoms of class 1 listed from the front of perm, the others from its end,
-// both in order; the number of the first goes to the header. The atoms before a
-// workgroup's own are counted by k_o3_count (CNT), or in a short list by the
-// workgroup itself, several loads of a thread in flight, which saves that launch
-// but grows with the square of |S|: all-expensive calls of a light two-species
-// model, counted by themselves / by k_o3_count: 20.9 / 14.1 ms on 1,024,000
-// atoms, 7.90 / 6.94 on 524,288.
-template <bool CNT>
+// both in order; the number of the first goes to the header. One launch: a second
+// one before it would wait for compute units where the cheap potential runs beside
+// it (a kept-list step of 128,000 atoms with one defect: 433 / 448 us). Every
+// workgroup counts the atoms before its own share by itself, several loads of a
+// thread in flight; there are at most kOrderBlocks of them, so the work grows with
+// |S| (a workgroup per 1024 atoms read |S|^2 / 2048: an all-expensive call of a light
+// two-species model on 1,024,000 atoms took 20.9 ms, now 14.4).
+constexpr int kOrderBlocks = 64;
+
 __global__ void __launch_bounds__(1024)
     k_o3_order(int *__restrict__ hdr, const int32_t *__restrict__ species,
                const int *__restrict__ S_idx, const float *__restrict__ A, int KAt, int nrad, int ns,
-               int scap, const int *__restrict__ counts, int *__restrict__ perm)
+               int scap, int *__restrict__ perm)
 {
     const int nS = hdr[H_NS];
-    const int b0 = blockIdx.x * 1024;
+    const int span = rules::o3_order_span(nS, gridDim.x);
+    const int b0 = blockIdx.x * span;
     if (b0 >= nS && blockIdx.x > 0)
         return;  // uniform across the workgroup
     __shared__ int part[16];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     int cnt = 0;
-    if constexpr (CNT) {
-        for (int k = tid; k < (int)blockIdx.x; k += 1024)
-            cnt += counts[k];
-    } else {
 #pragma unroll 8
-        for (int s = tid; s < b0; s += 1024)
-            cnt += o3_pure(s, species, S_idx, A, KAt, nrad, ns) ? 1 : 0;
+    for (int s = tid; s < b0; s += 1024)
+        cnt += o3_pure(s, species, S_idx, A, KAt, nrad, ns) ? 1 : 0;
+    int before = o3_block_sum(cnt, part);  // class-1 atoms before the next 1024
+    for (int c0 = b0; c0 < min(b0 + span, nS); c0 += 1024) {
+        const int s = c0 + tid;
+        const bool on = s < nS && o3_pure(s, species, S_idx, A, KAt, nrad, ns);
+        const unsigned long long msk = __ballot(on);
+        if (lane == 0)
+            part[w] = __popcll(msk);
+        __syncthreads();
+        int base = before;
+        for (int k = 0; k < 16; ++k) {
+            before += part[k];
+            base += k < w ? part[k] : 0;
+        }
+        __syncthreads();
+        if (s < nS) {
+            const int r = base + __popcll(msk & ((1ull << lane) - 1ull));
+            perm[on ? r : scap - 1 - (s - r)] = s;  // s - r atoms of the other class before it
+        }
     }
-    const int before = o3_block_sum(cnt, part);  // class-1 atoms before this workgroup's
-    const int s = b0 + tid;
-    const bool on = s < nS && o3_pure(s, species, S_idx, A, KAt, nrad, ns);
-    const unsigned long long msk = __ballot(on);
-    if (lane == 0)
-        part[w] = __popcll(msk);
-    __syncthreads();
-    int base = before, all = before;
-    for (int k = 0; k < 16; ++k) {
-        all += part[k];
-        base += k < w ? part[k] : 0;
-    }
-    if (s < nS) {
-        const int r = base + __popcll(msk & ((1ull << lane) - 1ull));
-        perm[on ? r : scap - 1 - (s - r)] = s;  // s - r atoms of the other class before it
-    }
-    if (tid == 0 && b0 + 1024 >= nS)
-        hdr[H_O3PURE] = all;
+    if (tid == 0 && b0 + span >= nS)
+        hdr[H_O3PURE] = before;
 }
 
 // QM 0 FP32, 1 BF16 dense stage; NC channels rounded up to 4 (<= 32); CLS 0
@@ -944,7 +929,7 @@ __global__ void __launch_bounds__(256, CLS == 1 ? 2 : 1)
     const int nS = hdr[H_NS];
     const int nC = CLS == 0 ? nS : (CLS == 1 ? hdr[H_O3PURE] : nS - hdr[H_O3PURE]);
     const int ntile = (nC + kO3Atoms - 1) / kO3Atoms;
-    const int lg = rules::o3_split_log(ntile, (int)gridDim.x, a.max_split, a.fill_split), G = 1 << lg;
+    const int lg = rules::o3_split_log(ntile, (int)gridDim.x, a.max_split, a.fill), G = 1 << lg;
     const int nitem = ntile * G;
     // the splits of one tile on one XCD: its A rows come from that XCD's L2
     // after the first fetch
@@ -1280,44 +1265,8 @@ hipError_t o3w_prepare(const Ctx &c)
     });
 }
 
-// The class lists (and the counts behind them) sit in the pair gradients, which the
-// pair adjoint of the same evaluation (or of a later backward) writes before
-// anything reads them: 3 cap floats per S atom, at least scap + blocks here.
-static int *o3w_perm(void *ws, const WsLayout &L) { return at<int>(ws, L.g); }
-
-static void o3w_lists(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, const int32_t *species,
-                      hipEvent_t ev0)
-{
-    const DevModel &m = c.m;
-    int *perm = o3w_perm(ws, L), *counts = perm + L.scap;
-    const int blocks = (L.scap + 1023) / 1024;
-    auto go = [&](auto kern, bool first, auto... rest) {
-        if (ev0)
-            hipExtLaunchKernelGGL(kern, dim3(blocks), dim3(1024), 0u, s, first ? ev0 : nullptr, nullptr, 0u,
-                                  at<int>(ws, L.hdr), species, at<int>(ws, L.S_idx), at<float>(ws, L.A), m.KAt,
-                                  m.nrad, m.ns, rest...);
-        else
-            kern<<<blocks, 1024, 0, s>>>(at<int>(ws, L.hdr), species, at<int>(ws, L.S_idx), at<float>(ws, L.A),
-                                         m.KAt, m.nrad, m.ns, rest...);
-    };
-    if (rules::o3_count_first(L.scap)) {
-        go(k_o3_count, true, counts);
-        go(k_o3_order<true>, false, L.scap, counts, perm);
-    } else {
-        go(k_o3_order<false>, true, L.scap, counts, perm);
-    }
-}
-
-static bool o3w_classes(const Ctx &c, const WsLayout &L) { return c.o3_classes && L.scap > 0; }
-
-void launch_ace_lists(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L, const int32_t *species)
-{
-    if (L.n > 0 && c.prec != MLMIX_FP64 && c.o3 == 2 && o3w_classes(c, L))
-        o3w_lists(s, c, ws, L, species, nullptr);
-}
-
 void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
-                    const int32_t *species, hipEvent_t ev0, hipEvent_t ev1, bool listed)
+                    const int32_t *species, hipEvent_t ev0, hipEvent_t ev1)
 {
     const DevModel &m = c.m;
     const char *base = static_cast<const char *>(m.base);
@@ -1340,9 +1289,12 @@ void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
     a.ns = m.ns;
     a.nrad = m.nrad;
     a.scap = L.scap;
-    a.perm = o3w_perm(ws, L);
-    const bool classes = o3w_classes(c, L);
-    a.max_split = classes ? c.o3_class_split : c.o3_max_split;
+    // the class lists sit in the pair gradients, which the pair adjoint of the same
+    // evaluation (or of a later backward) writes before anything reads them
+    int *perm = at<int>(ws, L.g);
+    a.perm = perm;
+    const bool classes = c.o3_classes && L.scap > 0;
+    a.max_split = c.o3_wide_split;
     // K order of a channel a's values b < n_rad: the full steps take b = NJ q + j
     // step by step (j), lane group by lane group (q)
     {
@@ -1366,11 +1318,11 @@ void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
         auto go = [&](auto kern, bool one, bool first, bool last) {
             const size_t lds = o3w_lds(c, one);
             const int per_cu = lds <= 80 * 1024 ? 2 : 1;
-            // class 2, few tiles as a rule and with most of the work, takes no second
-            // round of workgroups for a split: at all where one of them fills a CU's
-            // LDS, beyond the general split where two share it (an alloy, all of it
-            // class 2, then runs as one class does)
-            a.fill_split = !classes || one ? a.max_split : (per_cu == 1 ? 1 : c.o3_max_split);
+            // (class 1 fills the grid; the long tiles of the others take no second
+            // round: two species of 16 channels, lmax 1, an alloy of 8,192 atoms with
+            // 4,300 in S: 1.85 / 1.51 ms per 6 steps with 538 items on 512 workgroups /
+            // with 269)
+            a.fill = one;
             const int grid = (int)std::min<long>(std::max<long>(items, 1), 256L * per_cu);
             if (ev0)
                 hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), (uint32_t)lds, s, first ? ev0 : nullptr,
@@ -1382,9 +1334,13 @@ void launch_ace_o3w(hipStream_t s, const Ctx &c, void *ws, const WsLayout &L,
             go(k_ace_o3w<QM, NC, 0>, false, true, true);
             return;
         }
-        if (!listed)
-            o3w_lists(s, c, ws, L, species, ev0);
-        go(k_ace_o3w<QM, NC, 2>, false, listed, false);  // the long tiles first
+        const int blocks = std::min(kOrderBlocks, (L.scap + 1023) / 1024);
+        if (ev0)
+            hipExtLaunchKernelGGL(k_o3_order, dim3(blocks), dim3(1024), 0u, s, ev0, nullptr, 0u, hdr, species,
+                                  S_idx, A, m.KAt, m.nrad, m.ns, L.scap, perm);
+        else
+            k_o3_order<<<blocks, 1024, 0, s>>>(hdr, species, S_idx, A, m.KAt, m.nrad, m.ns, L.scap, perm);
+        go(k_ace_o3w<QM, NC, 2>, false, false, false);  // the long tiles first
         go(k_ace_o3w<QM, NC, 1>, true, false, true);
     });
 }

@@ -9,12 +9,12 @@ namespace rules {
 // count (1 .. 16) rounded up to a multiple of four, as the channels are.
 constexpr int padded_nrad(int nrad) { return (nrad + 3) & ~3; }
 
-// Class lists of the wide contraction: count the workgroups' atoms in a launch of
-// its own (1.7 us of a step) above this S capacity. Below, a workgroup counts the
-// atoms before it by itself, up to 64 rounds of them when S fills the capacity
-// (about 20 us of the 1.2 ms and more that such a call takes), a few when it holds
-// a tenth.
-constexpr bool o3_count_first(int scap) { return scap > 65536; }
+// S atoms of a workgroup of the class listing: whole thousands (of 1024), equal for
+// all of blocks workgroups.
+constexpr int o3_order_span(int nS, int blocks)
+{
+    return ((nS + 1023) / 1024 + blocks - 1) / blocks * 1024;
+}
 
 // Two atom classes in the wide contraction, for models of several species whose
 // contraction takes at least this many operations per S atom: the listing and the
@@ -31,15 +31,53 @@ constexpr bool o3_classes(int n_species, int channels, double flops)
 }
 
 // log2 of the workgroups that share a tile of the wide contraction, at most
-// max_split of them: up to fill_split the smallest number that fills the grid,
-// beyond it only one whose items still run in one round of workgroups.
-constexpr int o3_split_log(int ntile, int grid, int max_split, int fill_split)
+// max_split of them: the largest split whose items run in one round of workgroups,
+// or with fill the smallest that fills the grid.
+constexpr int o3_split_log(int ntile, int grid, int max_split, bool fill)
 {
     int lg = 0;
-    while ((1 << lg) < max_split && (((1 << lg) < fill_split && (long long)ntile << lg < grid) ||
-                                     (long long)ntile << (lg + 1) <= grid))
+    while ((1 << lg) < max_split && (fill ? (long long)ntile << lg < grid : (long long)ntile << (lg + 1) <= grid))
         ++lg;
     return lg;
+}
+
+// Weight of an order-3 contraction for the fork rule below, in FP32 operations per S
+// atom: form 1 the single-species form (its vector-ALU sparse stage runs at a third
+// of the dense stage's rate, reduced operands at eight times it), 2 the wide form
+// (slower per operation), 3 the FP64 form. In two classes the wide form weighs as
+// much as lets a kept list start the cheap potential late and a rebuilding call of
+// more than 3,000 atoms early: there the reverse slots delay the cheap potential
+// until it meets the few long tiles of the second class, which need compute units
+// to themselves (2 x 12 functions, lmax 4, 0.2 % of the second species, BF16, early /
+// late: a rebuilding call on 54,000 atoms with a cylinder 720 / 872 us, on 11,664 with
+// one defect 168 / 157; a kept list there 139 / 129).
+constexpr double o3_weight(int form, bool reduced, bool classes, double sparse, double dense)
+{
+    return form == 2 ? (classes ? 3e6 : 4.0 * (sparse + dense))
+                     : (form == 3 ? 3.0 : 1.0) * (3.0 * sparse + (reduced ? 0.125 : 1.0) * dense);
+}
+
+// Whether a mixed step of a single system starts the cheap potential on the second
+// stream after the atomic basis, to run beside the order-3 contraction, instead of
+// after the neighbour rows. Its workgroups (one wave per atom, all at once) keep the
+// few blocks of the compaction and the basis waiting when they start first, and a
+// long contraction hides them; after a short one they hold up the step's end.
+// Measured early / late with both in one process (n_rad functions, lmax):
+//  - a weight of 7e5 and more: FP32 12, 4 (1.2e6), 10 steps: 857 / 794 us on 2,000
+//    atoms, 1,085 / 1,033 on 11,664, one defect; 16, 5 (4.9e6), a kept-list call: 105 / 102
+//    us on 2,662, 402 / 375 on 128,000; FP64 12, 4 (3.5e6): 105 / 98 on 2,662; BF16 12, 4
+//    (7.5e5), 10 steps: 805 / 784 on 2,662, 1,029 / 1,017 on 11,664;
+//  - 4e5: FP32 12, 3, kept list: 139 / 144 us on 39,366, 335 / 323 on 128,000;
+//  - below: FP32 8, 3 (1.5e5): 136 / 143 us on 39,366, 310 / 323 on 128,000;
+//  - a call that rebuilds the list builds the reverse slots on that stream too, which
+//    few contractions hide: FP32 12, 4: 82 / 93 us on 4,394, 113 / 120 on 11,664, but 78 /
+//    77 on 2,000; FP64 12, 4 (3.5e6): 114 / 106 on 2,662, 153 / 161 on 11,664; FP32 16, 6
+//    (1e7): 179 / 168 on 2,662, 317 / 298 on 39,366.
+constexpr bool fork_after_basis(double weight, int n, bool rebuild)
+{
+    if (rebuild)
+        return weight >= 6.5e6 || (weight >= 3e6 && n <= 3000) || (weight >= 1.3e6 && n <= 2048);
+    return weight >= 7e5 || (weight >= 4e5 && n >= 100000);
 }
 
 }  // namespace rules

@@ -1,13 +1,13 @@
 """The class lists of the wide order-3 contraction over several workgroups of
-1024 S atoms: |S| on both sides of the workgroup's size, lists ranked by their
-own counts (capacities up to 65,536) and by counts of a launch before (above),
-and more tiles than workgroups. About one atom in a hundred is of
+1024 S atoms: |S| on both sides of the workgroup's size, capacities with a
+workgroup per 1024 atoms and above (65,536), where each takes several rounds, and
+more tiles than workgroups. About one atom in a hundred is of
 the second species, so both classes hold atoms of every workgroup.
 
 Tolerance against the oracle: FP32 rounds at 6e-8; a force sums up to about 1e4
 products (two and six channels, lmax 1), so independent roundings leave 6e-8 x
-1e2 = 6e-6 of the sum of magnitudes; 3e-5 of the largest force. The two ways
-of listing give the same order and so the same bits.
+1e2 = 6e-6 of the sum of magnitudes; 3e-5 of the largest force. The capacity
+does not change the order, and so not the bits.
 """
 import numpy as np
 import pytest
@@ -65,17 +65,17 @@ def test_several_workgroups(n_s):
     assert len(_check(w, O.MODE_MIXED, ref=ref)["S"]) == n_s
 
 
-def test_both_ways_of_listing():
+def test_capacity_does_not_matter():
     w = _with_s(_cell(33, 4, 1), 3100)  # 71,874 atoms
     print("|S| 3100, capacities 71,874 and 4,000", flush=True)
     ref = O.mixed(w, O.MODE_MIXED)
-    counted, alone = _check(w, O.MODE_MIXED, ref=ref), _check(w, O.MODE_MIXED, s_cap=4000)
+    all_atoms, few = _check(w, O.MODE_MIXED, ref=ref), _check(w, O.MODE_MIXED, s_cap=4000)
     for k in ("forces", "e_exp"):
-        assert np.array_equal(counted[k], alone[k]), k
+        assert np.array_equal(all_atoms[k], few[k]), k
 
 
-def test_above_the_single_launch():
-    w = _cell(33, 2, 1)
+def test_several_rounds():
+    w = _cell(33, 2, 1)  # two rounds of each workgroup
     print("|S| 71,874", flush=True)
     ref = O.mixed(w, O.MODE_ALL_EXPENSIVE)
     assert len(_check(w, O.MODE_ALL_EXPENSIVE, ref=ref)["S"]) == len(w["pos"])
