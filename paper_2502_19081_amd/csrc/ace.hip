@@ -1845,9 +1845,10 @@ static size_t blocks_lds(const Ctx &c, int ta, size_t tsz, int stage_w)
     return b;
 }
 
-// Launch shape of the order-3 blocks: MFMA stages for single-species FP32
-// models (FP64 models of several species and multi-species models keep the
-// VALU stages); tile of c.ace_tile atoms (default 4) with the block's
+// Launch shape of the order-3 blocks (models that no matrix-core form of the
+// contraction takes: FP64 of several species or more than 16 channels, FP32 of more
+// than 32 channels): MFMA stages for single-species FP32 models, else the VALU
+// stages; tile of c.ace_tile atoms (default 4) with the block's
 // weights staged in LDS (c.ace_stage_w, default on) — the best of a sweep
 // over 1-8 atoms with and without staging on the 8,193-atom workload; the
 // tile shrinks until the LDS tile fits 64 KiB.

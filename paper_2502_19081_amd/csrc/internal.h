@@ -208,11 +208,11 @@ struct Ctx {
     int max_ent_pb;        // Gaunt entries of the largest single block
     // order-3 contraction on the matrix cores: 0 no (VALU blocks), 1 the
     // single-species form (<= 16 channels, FP32/BF16/FP8 operands), 2 the wide
-    // form (FP32, any species count, <= 32 channels), 3 the FP64 form (single
-    // species, <= 16 channels)
+    // form (FP32 and BF16, any species count, <= 32 channels), 3 the FP64 form
+    // (single species, <= 16 channels)
     int o3 = 0;
     int max_lds = 65536;   // dynamic LDS a workgroup may use on this device
-    int basis_mfma = 1;    // atomic basis and pair adjoint on the matrix cores (FP32)
+    int basis_mfma = 1;    // atomic basis (any precision) and FP32 pair adjoint on the matrix cores
     int basis_chunks = -1; // basis in 64-slot passes: -1 above 65,536 atoms, 0 never, 1 always
     // second-stream fork after the rows (0), recorded after the basis (1), or recorded
     // after the rows and issued after the compaction (2); -1 automatic: 1 where

@@ -777,8 +777,8 @@ size_t o3v_lds_bytes(const Ctx &c)
 //
 // Several species: an atom of species 0 with no neighbour of another species
 // has exact zeros in every other species' channels, and most atoms of an
-// alloy's or an implanted crystal's S are of that kind. k_o3_order lists them
-// apart; their tiles (CLS = 1) run on the first species' channels alone (one
+// implanted crystal's S are of that kind where the host is species 0. For the
+// models that rules::o3_classes names, k_o3_order lists them apart; their tiles (CLS = 1) run on the first species' channels alone (one
 // channel tile in the sparse stage, n_rad of the nch channels a, one output
 // tile in the dense stage), the others (CLS = 2) as above. What is left out
 // are products with zeros and the D of channels whose A is zero, so every
@@ -1398,11 +1398,8 @@ __global__ void __launch_bounds__(256, 2)
     const int nS = hdr[H_NS];
     const int ntile = (nS + kO3Atoms - 1) / kO3Atoms;
     // the largest split whose items still run in one round of workgroups
-    int G = 1, lg = 0;
-    while (G < kO3MaxSplit && 2 * ntile * G <= (int)gridDim.x) {
-        G <<= 1;
-        ++lg;
-    }
+    // (MLMIX_O3_MAX_SPLIT is for the single-precision forms)
+    const int lg = rules::o3_split_log(ntile, (int)gridDim.x, kO3MaxSplit, false), G = 1 << lg;
     const int nitem = ntile * G;
     const int vb = xcd_major(blockIdx.x, gridDim.x);
     if (vb >= nitem)
