@@ -1753,7 +1753,7 @@ static int compute_impl(mlmix_ctx *ctx, hipStream_t s, void *ws, const WsLayout 
     // fork point then follows the region stage.
     const int fork_at = c.fork_at >= 0 ? c.fork_at
                         : L.nseg == 0 && !capturing &&
-                                rules::fork_after_basis(c.o3_weight, L.n, (mode & MLMIX_FORCE_REBUILD) != 0)
+                                rules::fork_after_basis(c.o3, c.o3_weight, L.n, (mode & MLMIX_FORCE_REBUILD) != 0)
                             ? 1
                             : 2;
     const bool late = fork_at == 1 && m != MLMIX_MODE_ALL_CHEAP && !masked;

@@ -72,11 +72,16 @@ constexpr double o3_weight(int form, bool reduced, bool classes, double sparse, 
 //  - a call that rebuilds the list builds the reverse slots on that stream too, which
 //    few contractions hide: FP32 12, 4: 82 / 93 us on 4,394, 113 / 120 on 11,664, but 78 /
 //    77 on 2,000; FP64 12, 4 (3.5e6): 114 / 106 on 2,662, 153 / 161 on 11,664; FP32 16, 6
-//    (1e7): 179 / 168 on 2,662, 317 / 298 on 39,366.
-constexpr bool fork_after_basis(double weight, int n, bool rebuild)
+//    (1e7): 179 / 168 on 2,662, 317 / 298 on 39,366;
+//  - a rebuilding call of 100,000 atoms and more, one vacancy per 6,000 atoms: FP32 16, 4
+//    (1.6e6): 1,063 / 1,007 us on 128,000, 2,047 / 1,877 on 250,000, 9,013 / 8,414 on
+//    1,024,000; BF16 16, 5 (3e6): 1,870 / 1,790 on 250,000 (with one defect 1,356 / 1,380); at
+//    12, 3 (4e5) no difference. The FP64 form (2,341 / 2,464 on 250,000) and two atom
+//    classes (BF16 2 x 12, 4: 2,475 / 2,890) stay early.
+constexpr bool fork_after_basis(int form, double weight, int n, bool rebuild)
 {
     if (rebuild)
-        return weight >= 6.5e6 || (weight >= 3e6 && n <= 3000) || (weight >= 1.3e6 && n <= 2048);
+        return weight >= 6.5e6 || (form == 1 && weight >= 7e5 && n >= 100000) || (weight >= 3e6 && n <= 3000) || (weight >= 1.3e6 && n <= 2048);
     return weight >= 7e5 || (weight >= 4e5 && n >= 100000);
 }
 

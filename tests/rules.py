@@ -15,7 +15,7 @@ extern "C" int o3_classes(int ns, int ch, double flops) { return rules::o3_class
 extern "C" int o3_split_log(int ntile, int grid, int most, int fill) { return rules::o3_split_log(ntile, grid, most, fill); }
 extern "C" double o3_weight(int form, int reduced, int classes, double sparse, double dense)
 { return rules::o3_weight(form, reduced, classes, sparse, dense); }
-extern "C" int fork_after_basis(double w, int n, int rebuild) { return rules::fork_after_basis(w, n, rebuild); }
+extern "C" int fork_after_basis(int form, double w, int n, int rebuild) { return rules::fork_after_basis(form, w, n, rebuild); }
 """
 
 
@@ -29,5 +29,5 @@ def load(folder):
     lib.o3_classes.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_double]
     d, i = ctypes.c_double, ctypes.c_int
     lib.o3_weight.argtypes, lib.o3_weight.restype = [i, i, i, d, d], d
-    lib.fork_after_basis.argtypes = [d, i, i]
+    lib.fork_after_basis.argtypes = [i, d, i, i]
     return lib

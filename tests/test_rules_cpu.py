@@ -66,15 +66,16 @@ LIGHT, USUAL, WIDE, WIDEST = (3.0e4, 6.0e4), (2.3e5, 4.9e5), (9.1e5, 2.15e6), (2
 
 def test_cheap_potential_starts_late_only_beside_a_contraction_that_hides_it(lib):
     def late(form, reduced, ops, n, rebuild, classes=0):
-        return bool(lib.fork_after_basis(lib.o3_weight(form, reduced, classes, *ops), n, rebuild))
+        return bool(lib.fork_after_basis(form, lib.o3_weight(form, reduced, classes, *ops), n, rebuild))
 
     for n in (250, 2000, 8191, 54000, 1000000):
-        assert not lib.fork_after_basis(0.0, n, 0)  # no order-3 contraction
+        assert not lib.fork_after_basis(0, 0.0, n, 0)  # no order-3 contraction
         assert not late(1, 0, LIGHT, n, 0)
         for form in (1, 3):
             assert late(form, 0, USUAL, n, 0) and late(form, 0, WIDE, n, 0)
         # the reverse slots of a call that rebuilds the list go on that stream too
-        assert not late(1, 0, USUAL, n, 1)
+        assert late(1, 0, USUAL, n, 1) == (n >= 100000)  # a long contraction covers both
+        assert not late(1, 0, LIGHT, n, 1) and not late(3, 0, USUAL, max(n, 4000), 1)
         assert late(1, 0, WIDEST, n, 1)
         # two atom classes: not where the second's long tiles meet the cheap potential
         for ops in (USUAL, WIDEST):
@@ -88,6 +89,7 @@ def test_cheap_potential_starts_late_only_beside_a_contraction_that_hides_it(lib
 def test_fork_rule_is_monotonic_in_the_weight(lib):
     weights = [0.0] + [10 ** (4 + k / 16) for k in range(64)]
     for n in (1, 2048, 2049, 3000, 3001, 99999, 100000, 2000000):
-        for rebuild in (0, 1):
-            got = [lib.fork_after_basis(w, n, rebuild) for w in weights]
-            assert got == sorted(got)
+        for form in (1, 2, 3):
+            for rebuild in (0, 1):
+                got = [lib.fork_after_basis(form, w, n, rebuild) for w in weights]
+                assert got == sorted(got)
