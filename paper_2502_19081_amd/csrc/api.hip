@@ -1487,7 +1487,7 @@ try {
     if (const char *e = std::getenv("MLMIX_O3_MAX_SPLIT")) {
         int v = std::atoi(e);
         if (v == 1 || v == 2 || v == 4 || v == 8 || v == 16)
-            c.o3_max_split = c.o3_wide_split = v;
+            c.o3_max_split = c.o3_wide_split = v;  // the FP64 form keeps kO3MaxSplit
     }
     c.o3_classes = rules::o3_classes(d.n_species, nch, ctx->flops[0]);
     if (const char *e = std::getenv("MLMIX_O3_CLASSES"))
